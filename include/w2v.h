@@ -215,8 +215,8 @@ int32_t w2v_pending_slots(int32_t D, int32_t window, int32_t K);
  * w2v_pending_slots() LDS slots instead of M_in, reads the row as (M_in row
  * + pending updates) while its word is in the window, and adds the slot to
  * M_in atomically when it releases the word: when the slot is needed for
- * another word, when 2 * window targets pass without the word, and at the
- * end of the sentence. Every update reaches M_in before the call returns.
+ * another word, when 2 * window targets have passed without the word and the
+ * next one does not hold it either, and at the end of the sentence. Every update reaches M_in before the call returns.
  * With one sentence in flight this changes only the order of the fp32
  * additions; with several, another sentence sees these updates late (as
  * late as the word stays in this sentence's window) and never loses them.

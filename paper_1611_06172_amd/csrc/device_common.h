@@ -107,6 +107,16 @@ __device__ __forceinline__ float f_swap_sum16(float a, float b) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Sums over the two halves / the pairs of 16-lane rows, in every lane.
+__device__ __forceinline__ float f_sum32(float a) { return f_swap_sum32(a, a); }
+
+__device__ __forceinline__ float f_sum16(float a) { return f_swap_sum16(a, a); }
+
+template <int kCtrl>
+__device__ __forceinline__ int i_dpp(int x) {
+  return __builtin_amdgcn_mov_dpp(x, kCtrl, 0xF, 0xF, false);
+}
+
 template <int kCtrl>
 __device__ __forceinline__ float f_dpp(float x) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), kCtrl, 0xF,
@@ -179,14 +189,10 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
-// Minimum of one int over the wave (every lane gets it).
-__device__ __forceinline__ int wave_min(int x) {
-  x = min(x, __shfl_xor(x, 32));
-  x = min(x, __shfl_xor(x, 16));
-  x = min(x, __shfl_xor(x, 8));
-  x = min(x, __shfl_xor(x, 4));
-  x = min(x, __shfl_xor(x, 2));
-  x = min(x, __shfl_xor(x, 1));
+// Sum of one int over the wave (every lane gets it).
+__device__ __forceinline__ int wave_sum_int(int x) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m);
   return x;
 }
 

@@ -8,12 +8,17 @@
 //   3. runs those targets' minibatches in sentence order through the fused
 //      minibatch (sgns_core.h), so every minibatch of a sentence sees the
 //      updates of the ones before it, while minibatches of different
-//      sentences interleave without locks (Hogwild, Sec. 1.1). The updates
-//      of cold input rows collect in a few LDS slots while their words stay
-//      in the window (assign_slots, PendingRows) and reach the matrix once.
-// It serves every compiled shape, including output blocks that take several
-// reductions. The export variant stops after step 2 and writes the
-// minibatches out.
+//      sentences interleave without locks (Hogwild, Sec. 1.1). While a
+//      minibatch's rows are on their way the next one's ids are staged.
+// Pending input-row updates (PendingSlots, EpochIo): consecutive targets of
+// a sentence share most of their input words, so a wavefront adds the
+// updates of a cold input row to an LDS slot instead of the matrix, reads
+// the row as (matrix row + its pending updates) while the word stays in the
+// window, and adds the slot to the matrix once, atomically, when it lets the
+// word go. The row traffic of the minibatch path is dominated by its writes;
+// this turns about 2 window writes of an input row into one.
+// k_export stops after step 2 and writes the minibatches out.
+#include <algorithm>
 #include <climits>
 #include <map>
 #include <mutex>
@@ -26,179 +31,361 @@
 
 namespace w2v {
 
-// Pending-update slots of a wavefront: lane s < nslots holds the word of
-// slot s (slot_id, -1 if free) and the retained index of the last target
-// that used it (slot_t). For the minibatch of target qj with distinct inputs
-// mb.ctx[0..n):
-//   * a word held in a slot is a hit;
-//   * any other word with id >= pend_from takes a free slot, else the least
+// slots[]: rows of 64 C floats in LDS, the updates a wavefront has made to an
+// input row and not yet added to the matrix (lane l's columns l + 64c at
+// offset 64c + l). Slot code of distinct input i of a minibatch (lane i):
+// -1: no slot, its update goes to the matrix at once; s < kSlotHeld: slot s,
+// empty, which takes this minibatch's update; kSlotHeld + s: slot s holds
+// pending updates of this word, which the read adds and to which this
+// minibatch's update is added. A lane reads and writes its own columns only.
+constexpr int kSlotHeld = 64;
+
+// Smallest value of lanes 0..15 (x of the other lanes is not used).
+__device__ __forceinline__ int row0_min(int x) {
+  x = min(x, i_dpp<kDppXor1>(x));
+  x = min(x, i_dpp<kDppXor2>(x));
+  x = min(x, i_dpp<kDppRowHalfMirror>(x));
+  x = min(x, i_dpp<kDppRowMirror>(x));
+  return uniform_int(x);
+}
+
+// Pending-update slots of a wavefront: lane s < count (at most 16) holds the
+// word of slot s (id, -1 if free) and the retained index of the last target
+// that used it (used). For the minibatch of target q with the distinct
+// inputs mb.in_id[0..n):
+//   * a word held in a slot is a hit (find);
+//   * any other word with id >= from takes a free slot, else the least
 //     recently used slot no input of this minibatch holds (whose pending
 //     updates flush(s, id) first adds to the matrix), else none (its update
-//     goes to the matrix at once).
-// The choice goes to mb.slot (PendingRows). Slots unused for more than
-// `expire` targets are flushed and freed first, so no update stays pending
-// after its word has left the window for good; the caller flushes every
-// slot at the end of a sentence.
-template <int NMAX, class Flush>
-__device__ __forceinline__ void assign_slots(MinibatchLds& mb, int n, int qj,
-                                             int expire, int nslots,
-                                             int pend_from, int lane,
-                                             int& slot_id, int& slot_t,
-                                             const Flush& flush) {
-  const bool mine = lane < nslots;
-  for (uint64_t old = __ballot(mine && slot_id >= 0 && slot_t < qj - expire);
-       old != 0ull; old &= old - 1ull) {
-    const int s = __builtin_ctzll(old);
-    flush(s, __builtin_amdgcn_readlane(slot_id, s));
-    if (lane == s) slot_id = -1;
-  }
-  int code = -1;       // lane i < n: slot code of input i
-  uint32_t done = 0u;  // inputs settled by the first pass
+//     goes to the matrix at once) (assign).
+// Slots that this target does not use and that were not used for more than
+// `expire` targets before it are flushed and freed, so no update stays
+// pending after its word has left the window for good; the caller flushes
+// every slot at the end of a sentence. The rows of a minibatch are read
+// before its slots are flushed: none of the flushed slots holds one of them.
+struct PendingSlots {
+  int count, from, expire;
+  int id, used;
+  uint64_t miss;  // inputs of the current minibatch that may take a slot
+
+  // Finds the slots of target q's words; returns lane i's slot code.
+  template <int NMAX>
+  __device__ __forceinline__ int find(const Minibatch& mb, int q, int lane) {
+    int code = -1;
+    miss = __ballot(lane < mb.n && mb.in_id >= from);
 #pragma unroll
-  for (int i = 0; i < NMAX; ++i) {
-    if (i < n) {
-      const int id = uniform_int(mb.ctx[i]);
-      const uint64_t hm = __ballot(mine && slot_id == id);
-      if (hm != 0ull || id < pend_from) done |= 1u << i;
-      if (hm != 0ull) {
-        const int s = __builtin_ctzll(hm);
-        if (lane == i) code = kSlotHeld + s;
-        if (lane == s) slot_t = qj;
+    for (int i = 0; i < NMAX; ++i) {
+      if (i < mb.n && ((miss >> i) & 1ull) != 0ull) {
+        const uint64_t held = __ballot(lane < count &&
+                                       id == __builtin_amdgcn_readlane(mb.in_id, i));
+        if (held != 0ull) {
+          const int s = __builtin_ctzll(held);
+          if (lane == i) code = kSlotHeld + s;
+          if (lane == s) used = q;
+          miss &= ~(1ull << i);
+        }
+      }
+    }
+    return code;
+  }
+
+  // Expires slots and gives slots to the words that have none.
+  template <class Flush>
+  __device__ __forceinline__ void assign(const Minibatch& mb, int q, int lane, int& code,
+                                         const Flush& flush) {
+    const bool mine = lane < count;
+    for (uint64_t old = __ballot(mine && id >= 0 && used < q - expire); old != 0ull;
+         old &= old - 1ull) {
+      const int s = __builtin_ctzll(old);
+      flush(s, __builtin_amdgcn_readlane(id, s));
+      if (lane == s) id = -1;
+    }
+    for (; miss != 0ull; miss &= miss - 1ull) {
+      const int i = __builtin_ctzll(miss);
+      // (last use + 1, slot): free slots first, then the least recently used.
+      const int key = !mine ? INT_MAX : id < 0 ? lane : (used + 1) * 16 + lane;
+      const int least = row0_min(key);
+      if (least >= (q + 1) * 16) break;  // every slot holds an input of this minibatch
+      const int s = least & 15;
+      if (least >= 16) flush(s, __builtin_amdgcn_readlane(id, s));
+      if (lane == i) code = s;
+      const int word = __builtin_amdgcn_readlane(mb.in_id, i);
+      if (lane == s) {
+        id = word;
+        used = q;
       }
     }
   }
+
+  // Flushes every slot.
+  template <class Flush>
+  __device__ __forceinline__ void drain(int lane, const Flush& flush) {
+    for (uint64_t held = __ballot(lane < count && id >= 0); held != 0ull;
+         held &= held - 1ull) {
+      const int s = __builtin_ctzll(held);
+      flush(s, __builtin_amdgcn_readlane(id, s));
+    }
+    id = -1;
+  }
+};
+
+// Rows of the live matrices (Core's Io): read coherently, updated by tier,
+// input rows with a slot code in the wavefront's pending slots.
+template <int C>
+struct EpochIo {
+  RowTiers<C> tiers;
+  float* M_in;
+  float* M_out;
+  float* slots;
+  PendingSlots pend;
+  int q;     // retained index of the current target
+  int code;  // lane i: slot code of input i
+
+  // Adds the pending updates of slot s to the M_in row of word id.
+  __device__ __forceinline__ void flush(int s, int id) const {
+    const float* p = slot_row(s);
+    float d[C];
 #pragma unroll
-  for (int i = 0; i < NMAX; ++i) {
-    if (i < n && ((done >> i) & 1u) == 0u) {
-      const int key = !mine ? INT_MAX : slot_id < 0 ? -1 : slot_t;
-      const int least = wave_min(key);
-      if (least < qj) {
-        const int s = __builtin_ctzll(__ballot(key == least));
-        if (least >= 0) flush(s, __builtin_amdgcn_readlane(slot_id, s));
-        if (lane == i) code = s;
-        if (lane == s) {
-          slot_id = uniform_int(mb.ctx[i]);
-          slot_t = qj;
+    for (int c = 0; c < C; ++c) d[c] = p[kWave * c];
+    tiers.add(0, M_in, id, d);
+  }
+  __device__ __forceinline__ void before_inputs(const Minibatch& mb) {
+    if (pend.count > 0)
+      pend.assign(mb, q, tiers.lane, code, [&](int s, int id) { flush(s, id); });
+  }
+
+  __device__ __forceinline__ void load_in(int id, bool ok, float (&r)[C]) const {
+    load_row<C, true>(M_in, id, tiers.ld, ok ? tiers.D : 0, tiers.lane, r);
+  }
+  __device__ __forceinline__ void load_out(int id, bool ok, float (&r)[C]) const {
+    load_row<C, true>(M_out, id, tiers.ld, ok ? tiers.D : 0, tiers.lane, r);
+  }
+  template <int N>
+  __device__ __forceinline__ void settle_in(const Minibatch& mb, float (&a)[N][C]) const {
+    const uint64_t split =
+        __ballot(tiers.lane < mb.n && mb.in_id < tiers.split_rows);
+    add_splits(0, split, [&](int i) { return __builtin_amdgcn_readlane(mb.in_id, i); }, a);
+    const uint64_t held = __ballot(code >= kSlotHeld);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if (((held >> i) & 1ull) != 0ull) {
+        const float* p = slot_row(__builtin_amdgcn_readlane(code, i) - kSlotHeld);
+#pragma unroll
+        for (int c = 0; c < C; ++c) a[i][c] += p[kWave * c];
+      }
+    }
+  }
+  template <int N>
+  __device__ __forceinline__ void settle_out(const Minibatch& mb, int k0,
+                                             float (&o)[N][C]) const {
+    // bit k: column k0 + k is a split row
+    const uint64_t neg =
+        __ballot(tiers.lane < mb.n_out - 1 && mb.neg_id < tiers.split_rows);
+    uint64_t split = k0 == 0 ? neg << 1 : neg >> (k0 - 1);
+    if (k0 == 0 && mb.target < tiers.split_rows) split |= 1ull;
+    add_splits(1, split & ((1ull << N) - 1ull),
+               [&](int k) {
+                 return k0 + k == 0 ? mb.target
+                                    : __builtin_amdgcn_readlane(mb.neg_id, (k0 + k - 1) & 63);
+               },
+               o);
+  }
+  // Adds the partial rows of the rows whose bits are set, one row after the
+  // other: split rows are few, and the code for a row is there once.
+  template <int N, class Id>
+  __device__ __forceinline__ void add_splits(int m, uint64_t rows, const Id& id,
+                                             float (&r)[N][C]) const {
+#pragma unroll 1
+    for (; rows != 0ull; rows &= rows - 1ull) {
+      const int i = __builtin_ctzll(rows);
+      float t[C];
+      tiers.split_sum(m, id(i), t);
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        if (j == i) {
+#pragma unroll
+          for (int c = 0; c < C; ++c) r[j][c] += t[c];
         }
       }
     }
   }
-  if (lane < n) mb.slot[lane] = code;
-  __syncthreads();
+  template <int N>
+  __device__ __forceinline__ void put_out(int, int id, const float (&o)[N],
+                                          const float (&g)[N], int c0) const {
+    tiers.update(1, M_out, id, o, g, c0);
+  }
+  // A slot's row is read, added to and written back rather than added to by
+  // LDS atomics: a ds_add_f32 of a wavefront costs the CU's LDS unit so much
+  // that 8 wavefronts per CU waited for it (5e6 uniform tokens at D = 300:
+  // 47 ms).
+  template <int N>
+  __device__ __forceinline__ void fetch_kept(int i, float (&kept)[N], int c0) const {
+    const int s = __builtin_amdgcn_readlane(code, i);
+    if (s >= kSlotHeld) {
+      const float* p = slot_row(s - kSlotHeld) + kWave * c0;
+#pragma unroll
+      for (int c = 0; c < N; ++c) kept[c] = p[kWave * c];
+    } else {
+#pragma unroll
+      for (int c = 0; c < N; ++c) kept[c] = 0.f;
+    }
+  }
+  template <int N>
+  __device__ __forceinline__ void put_in(int i, int id, const float (&row)[N],
+                                         const float (&g)[N], const float (&kept)[N],
+                                         int c0) const {
+    const int s = __builtin_amdgcn_readlane(code, i);
+    if (s < 0) {
+      tiers.update(0, M_in, id, row, g, c0);
+    } else {
+      float* p = slot_row(s & (kSlotHeld - 1)) + kWave * c0;
+#pragma unroll
+      for (int c = 0; c < N; ++c) p[kWave * c] = kept[c] + g[c];
+    }
+  }
+  __device__ __forceinline__ float* slot_row(int s) const {
+    return slots + s * (kWave * C) + tiers.lane;
+  }
+};
+
+// Sentences that run at once per CU in a default launch: the waves per SIMD
+// that the row registers of a shape leave, times the four SIMDs. How far
+// concurrent sentences drift from the sequential epoch depends on how many
+// there are, so this is part of what a launch computes, not only of how fast
+// it does: it follows from C and the size of a logit block alone, and the
+// registers below are held to it.
+constexpr int sentences_per_simd(int C, int nmax, bool several_blocks) {
+  if (nmax == 32) return !several_blocks && C == 1 ? 3 : 2;
+  if (nmax == 16) return several_blocks ? (C == 1 ? 3 : C <= 3 ? 2 : 1) : C <= 2 ? 3 : 2;
+  return several_blocks ? (C <= 2 ? 3 : C <= 5 ? 2 : 1) : C <= 4 ? 3 : 2;
 }
 
-// Waves per SIMD the register allocation must allow, where the default
-// allocation lands just above a residency step. With several output blocks
-// at C <= 2 (178 registers, 2 waves) a bound of 3 spills three registers;
-// with one block at C = 4 (175, 2 waves) a bound of 3 spills two, and at
-// C = 10 (256 + 20, 1 wave) a bound of 2 spills 26. Each measured faster
-// (D = 100, K = 15: +9%; D = 200, K = 5: +5%; D = 600, K = 5: +19%). The
-// bounds apply to the kernels of up to 10 input words (window <= 5);
-// elsewhere, and at C = 5 (3 waves: 29 spills, no LDS left for pending
-// rows, -8%), the next step up costs more than it gains.
+// Waves per SIMD the register allocation must allow.
 template <int C, int NMAX, bool kMulti>
 constexpr int epoch_waves_per_eu() {
-  if (NMAX > 10) return 1;
-  if (kMulti) return C <= 2 ? 3 : 1;
-  return C == 4 ? 3 : (C >= 10 ? 2 : 1);
+  return sentences_per_simd(C, NMAX, kMulti);
 }
 
-template <int C, int NMAX, bool kMulti, bool kExport>
+// The kernel's arguments, read again from the kernel argument segment: what
+// only the start of a sentence or of a batch of targets needs does not hold
+// scalar registers (or vector registers, spilled) in between.
+__device__ __forceinline__ EpochArgs reread_args() {
+  typedef const __attribute__((address_space(4))) EpochArgs* Segment;
+  Segment p = (Segment)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const EpochArgs*)p;
+}
+
+template <int C, int NMAX, bool kMulti>
 __global__ __launch_bounds__(kWave) __attribute__((
     amdgpu_waves_per_eu(epoch_waves_per_eu<C, NMAX, kMulti>()))) void k_epoch(EpochArgs a) {
   __shared__ SentenceLds sl;
-  __shared__ TargetBatch tb;
-  __shared__ MinibatchLds mb;
   extern __shared__ int32_t negs_lds[];  // [TB][K], then the pending slots
   const int lane = threadIdx.x;
   const int K = a.K;
   const bool want_loss = a.loss != nullptr;
-  const int TB = kExport ? kWave : a.target_batch;  // targets formed at once
-  float* const slot_rows = reinterpret_cast<float*>(negs_lds + TB * (K > 0 ? K : 1));
-  const int nslots = kExport ? 0 : a.pend_slots;
-  int slot_id = -1, slot_t = 0;
-  const RowTiers<C, false> io{a.part, a.split_rows, a.hot_rows, a.ld, a.D, lane};
-  // Adds the pending updates of slot s to the M_in row of word id.
-  auto flush = [&](int s, int id) {
-    const float* p = slot_rows + s * (kWave * C) + lane;
-    float d[C];
-#pragma unroll
-    for (int c = 0; c < C; ++c) d[c] = p[kWave * c];
-    io.add(0, a.M_in, id, d);
-  };
+  const int TB = a.target_batch;  // targets formed at once
+  EpochIo<C> io{{a.part, a.split_rows, a.hot_rows, a.ld, a.D, lane},
+                a.M_in,
+                a.M_out,
+                reinterpret_cast<float*>(negs_lds + TB * (K > 0 ? K : 1)),
+                {a.pend_slots, a.pend_from, 2 * a.w, -1, 0, 0ull},
+                0,
+                -1};
 
   int64_t n_mb = 0, sum_n = 0, raw = 0, rejected = 0, rows = 0;
   double lsum = 0.0, lcnt = 0.0;
   int bucket = -1;
 
   for (int64_t s = blockIdx.x; s < a.n_sent; s += gridDim.x) {
-    const int64_t sb = a.pos_begin + s * a.L;
-    const int64_t se = min(sb + (int64_t)a.L, a.pos_end);
+    const EpochArgs ka = reread_args();
+    const int64_t sb = ka.pos_begin + s * ka.L;
+    const int64_t se = min(sb + (int64_t)ka.L, ka.pos_end);
     const int len = (int)(se - sb);
     raw += len;
-    const int n_ret = keep_and_compact<kExport>(a, sb, len, lane, sl, rejected);
+    const int n_ret = keep_and_compact<false>(ka, sb, len, lane, sl, rejected);
 
     for (int q0 = 0; q0 < n_ret; q0 += TB) {
-      form_targets<kExport>(a, sb, q0, n_ret, lane, sl, tb, negs_lds, TB);
-      const int cnt = min(TB, n_ret - q0);
-      for (int j = 0; j < cnt; ++j) {
-        const int n = uniform_int(tb.n[j]);
-        if (n == 0) continue;
-        if (uniform_int(tb.bad[j]) != 0) {
-          ++rejected;
-          continue;
-        }
-        ++n_mb;
-        sum_n += n;
-        if constexpr (!kExport) {
-          const int qj = q0 + j;
-          const int lo = uniform_int(tb.lo[j]);
-          int ctx_id = 0;
-          if (lane < n) {
-            int jj = lo + lane;
-            if (jj >= qj) ++jj;
-            ctx_id = sl.ret_id[jj];
-          }
-          const int n_in = stage_inputs(lane, ctx_id, lane < n, mb);
+      uint64_t bad;
+      const FormedTarget t = form_targets(reread_args(), sb, q0, n_ret, lane, sl, negs_lds,
+                                          TB, bad);
+      uint64_t todo = __ballot(t.n > 0);
+      rejected += __popcll(todo & bad);
+      todo &= ~bad;
+      n_mb += __popcll(todo);
+      // One minibatch behind the ids: the turn that stages target q0 + j runs
+      // the minibatch staged in the turn before, whose rows are on their way.
+      Minibatch staged{};
+      int j = -1;
+      while (j >= 0 || todo != 0ull) {
+        const Minibatch mb = staged;
+        const int cur = j;
+        Core<C, NMAX, kMulti> core;
+        if (cur >= 0) core.load(io, mb);
+        j = -1;
+        if (todo != 0ull) {
+          j = __builtin_ctzll(todo);
+          todo &= todo - 1ull;
+          const int n = __builtin_amdgcn_readlane(t.n, j);
+          int jj = __builtin_amdgcn_readlane(t.lo, j) + lane;
+          if (jj >= q0 + j) ++jj;
+          const int ctx = lane < n ? sl.ret_id[jj] : 0;
           const int neg = lane < K ? negs_lds[j * K + lane] : 0;
-          const int n_out = stage_outputs(lane, sl.ret_id[qj], neg, K, mb);
-          rows += n_in + n_out;
-          if (nslots > 0)
-            assign_slots<NMAX>(mb, n_in, qj, 2 * a.w, nslots, a.pend_from, lane,
-                               slot_id, slot_t, flush);
-          else if (lane < n_in)
-            mb.slot[lane] = -1;
-          const PendingRows pend{slot_rows, mb.slot};
-          float loss_part = 0.f;
-          run_minibatch<C, NMAX, kMulti, true, false>(
-              a.M_in, a.M_out, a.M_in, a.M_out, a.ld, a.D, lane, n_in, n_out,
-              uniform_float(tb.alpha[j]), a.hot_rows, mb, want_loss,
-              loss_part, a.part, a.split_rows, TargetError(), pend);
-          if (want_loss) {
-            const int64_t p = sb + sl.ret_off[qj];
-            const int b = (int)(p * (int64_t)a.n_buckets / a.T);
-            if (b != bucket) {
-              if (bucket >= 0) flush_loss(a.loss, bucket, lsum, lcnt, lane);
-              bucket = b;
-            }
-            lsum += (double)loss_part;
-            if (lane == 0) lcnt += (double)n;
+          sum_n += n;
+          staged = stage_minibatch<(NMAX > 16)>(lane, ctx, (1ull << n) - 1ull,
+                                                __builtin_amdgcn_readlane(t.id, j), neg, K);
+          rows += staged.n + staged.n_out;
+        }
+        if (cur < 0) continue;
+        io.q = q0 + cur;
+        if (io.pend.count > 0) io.code = io.pend.template find<NMAX>(mb, io.q, lane);
+        float loss_part = 0.f;
+        core.run(io, lane, mb,
+                 __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t.alpha), cur)),
+                 want_loss, loss_part);
+        if (want_loss) {
+          const int b = __builtin_amdgcn_readlane(t.bucket, cur);
+          if (b != bucket) {
+            if (bucket >= 0) flush_loss(a.loss, bucket, lsum, lcnt, lane);
+            bucket = b;
           }
+          lsum += (double)loss_part;
+          lcnt += (double)__builtin_amdgcn_readlane(t.n, cur);
         }
       }
       __syncthreads();
     }
-    if constexpr (!kExport) {
-      for (uint64_t held = __ballot(lane < nslots && slot_id >= 0); held != 0ull;
-           held &= held - 1ull) {
-        const int s = __builtin_ctzll(held);
-        flush(s, __builtin_amdgcn_readlane(slot_id, s));
-      }
-      slot_id = -1;
-    }
+    io.pend.drain(lane, [&](int slot, int id) { io.flush(slot, id); });
   }
   if (want_loss && bucket >= 0) flush_loss(a.loss, bucket, lsum, lcnt, lane);
   flush_stats(a, lane, n_mb, sum_n, raw, rejected, rows);
+}
+
+// The minibatches of the epoch written out instead of run.
+__global__ __launch_bounds__(kWave) void k_export(EpochArgs a) {
+  __shared__ SentenceLds sl;
+  extern __shared__ int32_t negs_lds[];  // [kWave][K]
+  const int lane = threadIdx.x;
+  int64_t n_mb = 0, sum_n = 0, raw = 0, rejected = 0;
+  for (int64_t s = blockIdx.x; s < a.n_sent; s += gridDim.x) {
+    const int64_t sb = a.pos_begin + s * a.L;
+    const int64_t se = min(sb + (int64_t)a.L, a.pos_end);
+    const int len = (int)(se - sb);
+    raw += len;
+    const int n_ret = keep_and_compact<true>(a, sb, len, lane, sl, rejected);
+    for (int q0 = 0; q0 < n_ret; q0 += kWave) {
+      uint64_t bad;
+      const FormedTarget t =
+          form_targets(a, sb, q0, n_ret, lane, sl, negs_lds, kWave, bad);
+      export_targets(a, sb, q0, n_ret, lane, sl, t, negs_lds);
+      const uint64_t formed = __ballot(t.n > 0);
+      rejected += __popcll(formed & bad);
+      n_mb += __popcll(formed & ~bad);
+      sum_n += wave_sum_int(((formed & ~bad) >> lane) & 1ull ? t.n : 0);
+      __syncthreads();
+    }
+  }
+  flush_stats(a, lane, n_mb, sum_n, raw, rejected, 0);
 }
 
 // Partial rows of the split rows: cleared before an epoch, summed (in the
@@ -242,7 +429,7 @@ template <int C, int OMAX>
 __global__ __launch_bounds__(kWave) void k_epoch_grouped(EpochArgs a) {
   __shared__ SentenceLds sl;
   __shared__ TargetBatch tb;
-  __shared__ MinibatchLds mb;
+  __shared__ GroupRows mb;
   __shared__ GroupLds gl;
   extern __shared__ int32_t negs_lds[];  // [kWave][K]
   const int lane = threadIdx.x;
@@ -262,7 +449,7 @@ __global__ __launch_bounds__(kWave) void k_epoch_grouped(EpochArgs a) {
     const int n_ret = keep_and_compact<false>(a, sb, len, lane, sl, rejected);
 
     for (int q0 = 0; q0 < n_ret; q0 += kWave) {
-      form_targets<false>(a, sb, q0, n_ret, lane, sl, tb, negs_lds);
+      form_target_batch(a, sb, q0, n_ret, lane, sl, tb, negs_lds);
       const int cnt = min(kWave, n_ret - q0);
       for (int j0 = 0; j0 < cnt; j0 += G) {
         // Members: lane g < G holds the input count of target j0 + g.
@@ -407,10 +594,10 @@ using EpochKernel = void (*)(EpochArgs);
 // Kernel for C columns per lane, up to nmax input words, and K negatives:
 // the single-block variant when the K+1 output columns fit one reduction.
 static EpochKernel train_kernel_for(int C, int nmax, int K) {
-  const bool multi = K + 1 > kWave / (nmax > 0 ? nmax : 1);
+  const bool multi = K + 1 > Core<1, 10, false>::KB;
 #define W2V_PICK(c, n) \
   if (C == c && nmax == n) \
-    return multi ? k_epoch<c, n, true, false> : k_epoch<c, n, false, false>;
+    return multi ? k_epoch<c, n, true> : k_epoch<c, n, false>;
   W2V_TRAIN_SHAPES(W2V_PICK)
 #undef W2V_PICK
   return nullptr;
@@ -480,12 +667,14 @@ static TrainShape compute_train_shape(int C, int nmax, int K) {
   EpochKernel k = train_kernel_for(C, nmax, K);
   if (k == nullptr) return t;
   const void* f = reinterpret_cast<const void*>(k);
-  const int best = resident_blocks_per_cu(f, negatives_lds(K, 8));
+  const int best = std::min(resident_blocks_per_cu(f, negatives_lds(K, 8)),
+                       4 * sentences_per_simd(C, nmax, K + 1 > kWave / nmax));
   while (t.target_batch > 8 &&
          resident_blocks_per_cu(f, negatives_lds(K, t.target_batch)) < best)
     t.target_batch /= 2;
   const size_t negs = negatives_lds(K, t.target_batch);
-  t.blocks_per_cu = resident_blocks_per_cu(f, negs);
+  t.blocks_per_cu = std::min(resident_blocks_per_cu(f, negs),
+                        4 * sentences_per_simd(C, nmax, K + 1 > kWave / nmax));
   if (t.blocks_per_cu <= 0) return t;
   for (int n = kMaxPendingSlots; n >= 2; --n)
     if (resident_blocks_per_cu(f, negs + n * slot_bytes(C)) >= t.blocks_per_cu) {
@@ -563,7 +752,7 @@ hipError_t launch_grouped(int C, int omax, const EpochArgs& a, int grid,
 }
 
 hipError_t launch_export(const EpochArgs& a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL((k_epoch<1, 10, false, true>), dim3(grid), dim3(kWave),
+  hipLaunchKernelGGL(k_export, dim3(grid), dim3(kWave),
                      epoch_dyn_lds(a), s, a);
   return hipGetLastError();
 }

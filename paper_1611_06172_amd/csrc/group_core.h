@@ -18,6 +18,12 @@ namespace w2v {
 
 constexpr int kMaxGroup = 8;  // the host also bounds 2 window G <= 64
 
+// Distinct rows of a group, in LDS.
+struct GroupRows {
+  int ctx[kMaxInputs];   // input words (rows of M_in)
+  int out[kMaxOutputs];  // output words (rows of M_out)
+};
+
 struct GroupLds {
   int occ_id[kWave];                   // input occurrences: word
   int occ_g[kWave];                    // ... and member index
@@ -34,8 +40,8 @@ struct GroupLds {
 struct GroupError {
   const GroupLds* gl;
   int G;
-  __device__ __forceinline__ float operator()(const MinibatchLds&, int li,
-                                              int lk, float x, float,
+  __device__ __forceinline__ float operator()(int li,
+                                              int lk, float x,
                                               bool want_loss,
                                               float& loss_part) const {
     const float sp = 1.f / (1.f + __expf(x));    // sigma(-x)
@@ -72,12 +78,12 @@ struct GroupError {
 template <int C, int OMAX>
 __device__ __forceinline__ void run_group(const EpochArgs& a, int lane,
                                           int n_in, int n_out,
-                                          MinibatchLds& mb, const GroupLds& gl,
+                                          const GroupRows& mb, const GroupLds& gl,
                                           int G, bool want_loss,
                                           float& loss_part) {
   constexpr int IB = kWave / OMAX;
   constexpr int kSlots = IB * OMAX;
-  const RowTiers<C, false> io{a.part, a.split_rows, a.hot_rows, a.ld, a.D, lane};
+  const RowTiers<C> io{a.part, a.split_rows, a.hot_rows, a.ld, a.D, lane};
   const GroupError err{&gl, G};
   float o[OMAX][C], go[OMAX][C];
 #pragma unroll
@@ -120,7 +126,7 @@ __device__ __forceinline__ void run_group(const EpochArgs& a, int lane,
     const int lk = lane % OMAX;
     const bool valid = lane < kSlots && li < n_in && lk < n_out;
     float e_lane = 0.f;
-    if (valid) e_lane = err(mb, li, lk, x, 0.f, want_loss, loss_part);
+    if (valid) e_lane = err(li, lk, x, want_loss, loss_part);
 
 #pragma unroll
     for (int ii = 0; ii < IB; ++ii) {
@@ -139,13 +145,13 @@ __device__ __forceinline__ void run_group(const EpochArgs& a, int lane,
             }
           }
         }
-        io.update(0, a.M_in, uniform_int(mb.ctx[i0 + ii]), av[ii], g);
+        io.update(0, a.M_in, uniform_int(mb.ctx[i0 + ii]), av[ii], g, 0);
       }
     }
   }
 #pragma unroll
   for (int k = 0; k < OMAX; ++k)
-    if (k < n_out) io.update(1, a.M_out, uniform_int(mb.out[k]), o[k], go[k]);
+    if (k < n_out) io.update(1, a.M_out, uniform_int(mb.out[k]), o[k], go[k], 0);
 }
 
 }  // namespace w2v

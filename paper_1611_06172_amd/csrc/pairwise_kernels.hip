@@ -44,7 +44,7 @@ __device__ __forceinline__ void write_row(float* M, int id, int64_t ld, int D,
                                           int lane, int hot_rows,
                                           const float (&old)[C],
                                           const float (&g)[C]) {
-  update_row<C, false>(M, id, ld, D, lane, hot_rows, old, g);
+  update_row<C>(row_at(M, id, ld), D, lane, id < hot_rows, old, g);
 }
 
 template <int C>
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kWave) void k_epoch_pairwise(EpochArgs a) {
     const int n_ret = keep_and_compact<false>(a, sb, len, lane, sl, rejected);
 
     for (int q0 = 0; q0 < n_ret; q0 += kWave) {
-      form_targets<false>(a, sb, q0, n_ret, lane, sl, tb, negs_lds);
+      form_target_batch(a, sb, q0, n_ret, lane, sl, tb, negs_lds);
       const int cnt = min(kWave, n_ret - q0);
       for (int j = 0; j < cnt; ++j) {
         const int n = uniform_int(tb.n[j]);

@@ -7,7 +7,8 @@
 //    kept words into LDS with a ballot prefix count.
 //  * form_targets: forms up to 64 targets lane-parallel: window half-width
 //    (word 1), the K shared negatives (words 2.., one table read each), the
-//    decayed learning rate, and whether a negative id is out of range.
+//    decayed learning rate, and whether a negative id is out of range;
+//    form_target_batch leaves them in LDS, export_targets writes them out.
 #pragma once
 
 #include "device_common.h"
@@ -28,7 +29,6 @@ struct TargetBatch {
   int32_t lo[kWave];              // first retained index of the window
   int32_t n[kWave];               // number of input words
   float alpha[kWave];
-  uint64_t mask[kWave];           // bit k: negative k equals the target
   int32_t bad[kWave];             // a negative id outside [0, V)
 };
 
@@ -75,69 +75,116 @@ __device__ __forceinline__ int keep_and_compact(const EpochArgs& a, int64_t sb,
   return n_ret;
 }
 
-// Forms targets q0 + lane (lane < n_batch <= 64, q0 + lane < n_ret) into tb
-// and their negatives into negs[lane * K + k]. The export variant also
-// writes the minibatches out.
-template <bool kExport>
-__device__ __forceinline__ void form_targets(const EpochArgs& a, int64_t sb,
-                                             int q0, int n_ret, int lane,
-                                             const SentenceLds& sl,
-                                             TargetBatch& tb, int32_t* negs,
-                                             int n_batch = kWave) {
+// One target as formed, in one lane.
+struct FormedTarget {
+  int id = -1;        // the target word
+  int lo = 0;         // first retained index of the window
+  int n = 0;          // number of input words (0: no minibatch)
+  float alpha = 0.f;
+  int bucket = 0;     // loss bucket (formed only with a loss)
+};
+
+// Forms targets q0 + j, j < TB (TB a power of two up to 64, q0 + j < n_ret):
+// lane j returns target j, its negatives go to negs[j K + k], and `bad` gets
+// bit j where one of them is outside [0, V). The 64 / TB lanes l = j mod TB
+// share target j: lane l takes every (64 / TB)-th Philox block from block
+// l / TB on, and the table reads of a block are all in flight before any is
+// used (one by one, each a random access to a table of up to 400 MB, they
+// were 7% of the epoch's cycles at K = 64).
+__device__ __forceinline__ FormedTarget form_targets(const EpochArgs& a, int64_t sb,
+                                                     int q0, int n_ret, int lane,
+                                                     const SentenceLds& sl,
+                                                     int32_t* negs, int TB,
+                                                     uint64_t& bad) {
   const uint64_t e = (uint64_t)a.epoch;
   const int K = a.K;
   const int w = a.w;
-  const int q = q0 + lane;
-  if (q < n_ret && lane < n_batch) {
+  const int j = lane & (TB - 1);
+  const int q = q0 + j;
+  const int share = kWave / TB;
+  FormedTarget t;
+  bool bad_id = false;
+  if (q < n_ret) {
     const int64_t p = sb + sl.ret_off[q];
-    const int t = sl.ret_id[q];
-    U64x4 blk = stream_block(a.seed, (uint64_t)p, e, 0);
-    const int h = w - (int)scale_draw(word_of(blk, 1), (uint64_t)w);
-    const int lo = max(q - h, 0);
-    const int hi = min(q + h, n_ret - 1);
-    const int n = hi - lo;
-    uint64_t mask = 0;
-    int bad = 0;
-    int cur = 0;
-    for (int k = 0; k < K; ++k) {
-      const int word = 2 + k;
-      if ((word >> 3) != cur) {
-        cur = word >> 3;
-        blk = stream_block(a.seed, (uint64_t)p, e, (uint64_t)cur);
+    t.id = sl.ret_id[q];
+    const int n_blocks = (K + 9) >> 3;  // words 0 .. K + 1
+    for (int b = (int)((unsigned)lane / (unsigned)TB); b < n_blocks; b += share) {
+      const U64x4 blk = stream_block(a.seed, (uint64_t)p, e, (uint64_t)b);
+      if (b == 0) {
+        const int h = w - (int)scale_draw(word_of(blk, 1), (uint64_t)w);
+        t.lo = max(q - h, 0);
+        t.n = min(q + h, n_ret - 1) - t.lo;
       }
-      const uint32_t r = word_of(blk, word & 7);
-      const int neg = a.table[scale_draw(r, (uint64_t)a.table_size)];
-      bad |= (neg < 0 || neg >= a.V);
-      if (neg == t) mask |= 1ull << k;
-      negs[lane * K + k] = neg;
-    }
-    const float alpha =
-        decayed_alpha(a.alpha0, a.min_frac, a.epoch, a.n_epochs, a.T, p);
-    tb.lo[lane] = lo;
-    tb.n[lane] = n;
-    tb.alpha[lane] = alpha;
-    tb.mask[lane] = mask;
-    tb.bad[lane] = bad;
-    if constexpr (kExport) {
-      const int64_t r = p - a.pos_begin;
-      if (n == 0) {
-        a.out_targets[r] = -1;
-      } else {
-        a.out_targets[r] = t;
-        for (int i = 0; i < 2 * w; ++i) {
-          int id = -1;
-          if (i < n) id = sl.ret_id[lo + i + (lo + i >= q ? 1 : 0)];
-          a.out_ctx[r * 2 * w + i] = id;
-        }
-        for (int k = 0; k < K; ++k) {
-          a.out_negs[r * K + k] = negs[lane * K + k];
-          a.out_mask[r * K + k] = (uint8_t)((mask >> k) & 1ull);
-        }
-        a.out_alpha[r] = alpha;
+      const int k0 = 8 * b - 2;  // negative of the block's word 0
+      int neg[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int k = k0 + i;
+        neg[i] = 0;
+        if (k >= 0 && k < K)
+          neg[i] = a.table[scale_draw(word_of(blk, i), (uint64_t)a.table_size)];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int k = k0 + i;
+        bad_id |= neg[i] < 0 || neg[i] >= a.V;
+        if (k >= 0 && k < K) negs[j * K + k] = neg[i];
       }
     }
+    t.alpha = decayed_alpha(a.alpha0, a.min_frac, a.epoch, a.n_epochs, a.T, p);
+    if (a.loss != nullptr) t.bucket = (int)(p * (int64_t)a.n_buckets / a.T);
+  }
+  bad = __ballot(bad_id);
+  for (int s = kWave / 2; s >= TB; s /= 2) bad |= bad >> s;
+  if (TB < kWave) {
+    bad &= (1ull << TB) - 1ull;
+    if (lane >= TB) t.n = 0;
   }
   __syncthreads();
+  return t;
+}
+
+// The same for the 64 targets q0 .. q0 + 63, into LDS.
+__device__ __forceinline__ void form_target_batch(const EpochArgs& a, int64_t sb,
+                                                  int q0, int n_ret, int lane,
+                                                  const SentenceLds& sl,
+                                                  TargetBatch& tb, int32_t* negs) {
+  uint64_t bad;
+  const FormedTarget t = form_targets(a, sb, q0, n_ret, lane, sl, negs, kWave, bad);
+  tb.lo[lane] = t.lo;
+  tb.n[lane] = t.n;
+  tb.alpha[lane] = t.alpha;
+  tb.bad[lane] = (int)((bad >> lane) & 1ull);
+  __syncthreads();
+}
+
+// Writes the formed targets q0 .. q0 + 63 out (minibatch export).
+__device__ __forceinline__ void export_targets(const EpochArgs& a, int64_t sb, int q0,
+                                               int n_ret, int lane,
+                                               const SentenceLds& sl,
+                                               const FormedTarget& t,
+                                               const int32_t* negs) {
+  const int K = a.K;
+  const int w = a.w;
+  const int q = q0 + lane;
+  if (q >= n_ret) return;
+  const int64_t r = sb + sl.ret_off[q] - a.pos_begin;
+  if (t.n == 0) {
+    a.out_targets[r] = -1;
+    return;
+  }
+  a.out_targets[r] = t.id;
+  for (int i = 0; i < 2 * w; ++i) {
+    int id = -1;
+    if (i < t.n) id = sl.ret_id[t.lo + i + (t.lo + i >= q ? 1 : 0)];
+    a.out_ctx[r * 2 * w + i] = id;
+  }
+  for (int k = 0; k < K; ++k) {
+    const int neg = negs[lane * K + k];
+    a.out_negs[r * K + k] = neg;
+    a.out_mask[r * K + k] = (uint8_t)(neg == t.id);
+  }
+  a.out_alpha[r] = t.alpha;
 }
 
 // Adds a wave's loss sums for one bucket (lane 0 holds the input count).

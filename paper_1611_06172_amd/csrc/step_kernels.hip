@@ -10,6 +10,7 @@
 //      rounding per element, so the result does not depend on the order in
 //      which the atomics landed beyond fp64 rounding.
 #include "kernel_args.h"
+#include "batch_ids.h"
 #include "sgns_core.h"
 
 namespace w2v {
@@ -20,41 +21,71 @@ __global__ __launch_bounds__(256) void k_zero(double* p, int64_t n) {
     p[i] = 0.0;
 }
 
+// Rows of the unchanged matrices (Core's Io); updates are added to the
+// delta buffers.
+template <int C>
+struct StepIo {
+  const StepArgs& a;
+  int lane;
+
+  __device__ __forceinline__ void load_in(int id, bool ok, float (&r)[C]) const {
+    load_row<C, false>(a.M_in, id, a.ld, ok ? a.D : 0, lane, r);
+  }
+  __device__ __forceinline__ void load_out(int id, bool ok, float (&r)[C]) const {
+    load_row<C, false>(a.M_out, id, a.ld, ok ? a.D : 0, lane, r);
+  }
+  template <int N>
+  __device__ __forceinline__ void settle_in(const Minibatch&, float (&)[N][C]) const {}
+  template <int N>
+  __device__ __forceinline__ void settle_out(const Minibatch&, int, float (&)[N][C]) const {}
+  __device__ __forceinline__ void before_inputs(const Minibatch&) const {}
+  template <int N>
+  __device__ __forceinline__ void fetch_kept(int, float (&)[N], int) const {}
+  template <int N>
+  __device__ __forceinline__ void add(double* d, int id, const float (&g)[N], int c0) const {
+    double* row = row_at(d, id, a.ld);
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+      const int col = lane + kWave * (c0 + c);
+      if (col < a.D) unsafeAtomicAdd(row + col, (double)g[c]);
+    }
+  }
+  template <int N>
+  __device__ __forceinline__ void put_out(int, int id, const float (&)[N],
+                                          const float (&g)[N], int c0) const {
+    add(a.dM_out, id, g, c0);
+  }
+  template <int N>
+  __device__ __forceinline__ void put_in(int, int id, const float (&)[N],
+                                         const float (&g)[N], const float (&)[N],
+                                         int c0) const {
+    add(a.dM_in, id, g, c0);
+  }
+};
+
 template <int C, int NMAX, bool kMulti>
 __global__ __launch_bounds__(kWave) void k_step(StepArgs a) {
-  __shared__ MinibatchLds mb;
   const int lane = threadIdx.x;
   int64_t applied = 0, sum_n = 0, rejected = 0, rows = 0;
   for (int64_t b = blockIdx.x; b < a.B; b += gridDim.x) {
-    const int t = a.targets[b];
-    int bad = (t < 0 || t >= a.V);
-    // input words: present ids compacted in order; -1 = absent
-    int c = -1;
-    if (lane < a.N) c = a.contexts[b * a.N + lane];
-    bad |= (c < -1 || c >= a.V);
-    const bool present = c >= 0;
-    const int n = __popcll(__ballot(present));
-    const int n_in = stage_inputs(lane, c, present, mb);
-    int neg = 0;
-    if (lane < a.K) {
-      neg = a.negatives[b * a.K + lane];
-      bad |= (neg < 0 || neg >= a.V);
-    }
-    const bool any_bad = __ballot(bad != 0) != 0ull;
-    const int n_out = stage_outputs(lane, t, neg, a.K, mb);
-    if (any_bad) {
+    BatchIds ids;
+    const bool bad = read_batch_ids(a, b, lane, ids);
+    if (bad) {
       ++rejected;
-    } else if (n > 0) {
-      ++applied;
-      sum_n += n;
-      rows += n_in + n_out;
-      const float alpha = a.alpha != nullptr ? a.alpha[b] : a.alpha_scalar;
-      float unused = 0.f;
-      run_minibatch<C, NMAX, kMulti, false, true>(a.M_in, a.M_out, a.dM_in, a.dM_out,
-                                          a.ld, a.D, lane, n_in, n_out, alpha,
-                                          0, mb, false, unused);
+      continue;
     }
-    __syncthreads();
+    const int n = __popcll(ids.present);
+    if (n == 0) continue;
+    const Minibatch mb = stage_minibatch<(NMAX > 16)>(lane, ids.ctx, ids.present,
+                                                      ids.target, ids.neg, a.K);
+    StepIo<C> io{a, lane};
+    Core<C, NMAX, kMulti> core;
+    core.load(io, mb);
+    ++applied;
+    sum_n += n;
+    rows += mb.n + mb.n_out;
+    float unused = 0.f;
+    core.run(io, lane, mb, a.alpha != nullptr ? a.alpha[b] : a.alpha_scalar, false, unused);
   }
   if (lane == 0) report_bad_ids(a.status, rejected);
   if (a.stats != nullptr && lane == 0) {
@@ -87,7 +118,7 @@ __global__ __launch_bounds__(256) void k_finalize(float* M, const double* dM,
 using StepKernel = void (*)(StepArgs);
 
 static StepKernel step_kernel_for(int C, int nmax, int K) {
-  const bool multi = K + 1 > kWave / nmax;
+  const bool multi = K + 1 > Core<1, 10, false>::KB;
 #define W2V_PICK(c, n) \
   if (C == c && nmax == n) return multi ? k_step<c, n, true> : k_step<c, n, false>;
   W2V_STEP_SHAPES(W2V_PICK)

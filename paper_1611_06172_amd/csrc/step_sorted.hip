@@ -4,7 +4,7 @@
 //
 //   1. k_stage: one wavefront per minibatch computes its updates from the
 //      unchanged matrices (sgns_core.h) and writes them to staging rows
-//      (StagedRows) instead of applying them. Each staging row gets a sort
+//      (StageIo) instead of applying them. Each staging row gets a sort
 //      key naming the matrix row it updates: id for M_in, V + id for M_out,
 //      2V for an unused staging row;
 //   2. one stable radix sort of (key, staging index) pairs (radix_sort.hip),
@@ -25,6 +25,7 @@
 // per update, the keys, and one read and write per touched row.
 #include <hip/hip_runtime.h>
 
+#include "batch_ids.h"
 #include "kernel_args.h"
 #include "sgns_core.h"
 
@@ -33,56 +34,91 @@ namespace w2v {
 constexpr int kChunk = 64;   // sorted entries per wavefront (one per lane)
 constexpr int kBatch = 8;    // rows loaded before they are added
 
+// Rows of the unchanged matrices (Core's Io); the update of distinct input i
+// goes to row i of `in`, that of output column k to row k of `out`.
+template <int C>
+struct StageIo {
+  const SortedStepArgs& a;
+  float* in;
+  float* out;
+  int lane;
+
+  __device__ __forceinline__ void load_in(int id, bool ok, float (&r)[C]) const {
+    load_row<C, false>(a.M_in, id, a.ld, ok ? a.D : 0, lane, r);
+  }
+  __device__ __forceinline__ void load_out(int id, bool ok, float (&r)[C]) const {
+    load_row<C, false>(a.M_out, id, a.ld, ok ? a.D : 0, lane, r);
+  }
+  template <int N>
+  __device__ __forceinline__ void settle_in(const Minibatch&, float (&)[N][C]) const {}
+  template <int N>
+  __device__ __forceinline__ void settle_out(const Minibatch&, int, float (&)[N][C]) const {}
+  __device__ __forceinline__ void before_inputs(const Minibatch&) const {}
+  template <int N>
+  __device__ __forceinline__ void fetch_kept(int, float (&)[N], int) const {}
+  template <int N>
+  __device__ __forceinline__ void put(float* row, const float (&g)[N], int c0) const {
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+      const int col = lane + kWave * (c0 + c);
+      if (col < a.D) row[col] = g[c];
+    }
+  }
+  template <int N>
+  __device__ __forceinline__ void put_out(int k, int, const float (&)[N],
+                                          const float (&g)[N], int c0) const {
+    put(out + k * a.ld, g, c0);
+  }
+  template <int N>
+  __device__ __forceinline__ void put_in(int i, int, const float (&)[N],
+                                         const float (&g)[N], const float (&)[N],
+                                         int c0) const {
+    put(in + i * a.ld, g, c0);
+  }
+};
+
 template <int C, int NMAX, bool kMulti>
 __global__ __launch_bounds__(kWave) void k_stage(SortedStepArgs a) {
-  __shared__ MinibatchLds mb;
   const int lane = threadIdx.x;
   const int n_slots_out = a.K + 1;
   int64_t applied = 0, sum_n = 0, rejected = 0, rows = 0;
   for (int64_t b = blockIdx.x; b < a.B; b += gridDim.x) {
-    const int t = a.targets[b];
-    int bad = (t < 0 || t >= a.V);
-    int c = -1;
-    if (lane < a.N) c = a.contexts[b * a.N + lane];
-    bad |= (c < -1 || c >= a.V);
-    const bool present = c >= 0;
-    const int n = __popcll(__ballot(present));
-    const int n_in = stage_inputs(lane, c, present, mb);
-    int neg = 0;
-    if (lane < a.K) {
-      neg = a.negatives[b * a.K + lane];
-      bad |= (neg < 0 || neg >= a.V);
-    }
-    const bool any_bad = __ballot(bad != 0) != 0ull;
-    const int n_out = stage_outputs(lane, t, neg, a.K, mb);
-    const bool use = !any_bad && n > 0;
-    // Keys of this minibatch's staging rows (2V where nothing is staged).
+    BatchIds ids;
+    const bool bad = read_batch_ids(a, b, lane, ids);
+    const int n = __popcll(ids.present);
+    const bool use = !bad && n > 0;
+    const Minibatch mb = stage_minibatch<(NMAX > 16)>(lane, ids.ctx, ids.present,
+                                                      ids.target, ids.neg, a.K);
     const int64_t in0 = b * a.N, out0 = b * n_slots_out;
+    StageIo<C> io{a, a.stage_in + in0 * a.ld, a.stage_out + out0 * a.ld, lane};
+    Core<C, NMAX, kMulti> core;
+    if (use) core.load(io, mb);
+    // Keys of this minibatch's staging rows (2V where nothing is staged).
     const uint32_t unused = 2u * (uint32_t)a.V;
     if (lane < a.N) {
-      a.key_in[in0 + lane] = (use && lane < n_in) ? (uint32_t)mb.ctx[lane] : unused;
+      a.key_in[in0 + lane] = (use && lane < mb.n) ? (uint32_t)mb.in_id : unused;
       a.val_in[in0 + lane] = (int32_t)(in0 + lane);
     }
-    for (int k = lane; k < n_slots_out; k += kWave) {
-      a.key_out[out0 + k] =
-          (use && k < n_out) ? (uint32_t)a.V + (uint32_t)mb.out[k] : unused;
-      a.val_out[out0 + k] = (int32_t)(a.out_base + out0 + k);
+    if (lane == 0) {
+      a.key_out[out0] = use ? (uint32_t)a.V + (uint32_t)mb.target : unused;
+      a.val_out[out0] = (int32_t)(a.out_base + out0);
     }
-    if (any_bad) {
+    if (lane < a.K) {
+      a.key_out[out0 + 1 + lane] = (use && lane + 1 < mb.n_out)
+                                       ? (uint32_t)a.V + (uint32_t)mb.neg_id
+                                       : unused;
+      a.val_out[out0 + 1 + lane] = (int32_t)(a.out_base + out0 + 1 + lane);
+    }
+    if (bad) {
       ++rejected;
-    } else if (n > 0) {
+    } else if (use) {
       ++applied;
       sum_n += n;
-      rows += n_in + n_out;
-      const float alpha = a.alpha != nullptr ? a.alpha[b] : a.alpha_scalar;
-      float unused = 0.f;
-      const StagedRows stage{a.stage_in + in0 * a.ld, a.stage_out + out0 * a.ld,
-                             a.ld, a.D};
-      run_minibatch<C, NMAX, kMulti, false, false, TargetError, StagedRows>(
-          a.M_in, a.M_out, a.M_in, a.M_out, a.ld, a.D, lane, n_in, n_out, alpha,
-          0, mb, false, unused, nullptr, 0, TargetError(), stage);
+      rows += mb.n + mb.n_out;
+      float no_loss = 0.f;
+      core.run(io, lane, mb, a.alpha != nullptr ? a.alpha[b] : a.alpha_scalar, false,
+               no_loss);
     }
-    __syncthreads();
   }
   if (lane == 0) report_bad_ids(a.status, rejected);
   if (a.stats != nullptr && lane == 0) {
@@ -365,7 +401,7 @@ using StageKernel = void (*)(SortedStepArgs);
 using ReduceKernel = void (*)(ReduceArgs);
 
 static StageKernel stage_kernel_for(int C, int nmax, int K) {
-  const bool multi = K + 1 > kWave / nmax;
+  const bool multi = K + 1 > Core<1, 10, false>::KB;
 #define W2V_PICK(c, n) \
   if (C == c && nmax == n) return multi ? k_stage<c, n, true> : k_stage<c, n, false>;
   W2V_SORTED_SHAPES(W2V_PICK)

@@ -1,0 +1,75 @@
+"""The fused minibatch (sgns_core.h) at the sizes where its tiles change: 1 to
+32 input rows (tiles of 8, reduced as 2, 4, 6 or 8 rows), 0 to 64 negatives
+(one block of 6 output columns, blocks of 8, blocks of 4 for rows of more
+than 384 columns, remainders of 1 to 8 columns), every compiled row length.
+Each batch holds every input count from 0 to N, over so few words that most
+minibatches repeat words and draw their own target as a negative."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1611_06172_amd import inputs, w2v
+from gpu_util import scaled_error, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# |gpu - oracle| <= 1e-5 S, S the magnitude of the summands of an element:
+# fp32 evaluation of sums of up to 65 products and one rounding (2.4e-7 S
+# measured at the kernel-test size).
+BAR = 1e-5
+
+
+@pytest.mark.parametrize("N,K,D", [
+    (1, 0, 1), (2, 5, 64), (3, 6, 65), (10, 5, 300), (9, 7, 128), (10, 8, 129),
+    (10, 15, 320), (10, 16, 384), (10, 5, 385), (10, 14, 512), (10, 63, 600),
+    (10, 64, 640), (10, 17, 100), (16, 5, 200), (15, 25, 320), (16, 33, 192),
+    (32, 4, 64), (31, 64, 128), (17, 9, 100),
+])
+@pytest.mark.parametrize("srt", [False, True])
+def test_tiles_match_the_oracle(N, K, D, srt):
+    B, V = 6 * (N + 1), 40
+    rng = np.random.Generator(np.random.PCG64(100 * N + K))
+    t = rng.integers(0, V, B).astype(np.int32)
+    c = rng.integers(0, V, (B, N)).astype(np.int32)
+    n = rng.integers(0, V, (B, K)).astype(np.int32)
+    # minibatch b has b mod (N + 1) input words: first its leading slots,
+    # then (odd rounds) slots spread over the row
+    for b in range(B):
+        count = b % (N + 1)
+        keep = np.arange(N) < count
+        if (b // (N + 1)) % 2:
+            keep = rng.permutation(keep)
+        c[b, ~keep] = -1
+    M_in = inputs.init_matrix(V, D, "normal", 4)
+    M_out = inputs.init_matrix(V, D, "normal", 5)
+    alpha = (rng.random(B) * 0.05).astype(np.float32)
+    oi, oo, S_in, S_out = oracle.step_batch(t, c, n, M_in, M_out, alpha)
+    gi, go = to_dev(M_in), to_dev(M_out)
+    w2v.step_batch(to_dev(t), to_dev(c), to_dev(n), gi, go, to_dev(alpha), sorted=srt)
+    assert scaled_error(gi.cpu().numpy(), oi, S_in) <= BAR
+    assert scaled_error(go.cpu().numpy(), oo, S_out) <= BAR
+
+
+@pytest.mark.parametrize("window,K,D", [(1, 6, 64), (3, 8, 100), (8, 40, 70), (16, 17, 64),
+                                        (5, 5, 640), (5, 23, 513)])
+def test_serialised_epoch_at_block_borders(window, K, D):
+    """One sentence in flight against the oracle's sequential epoch (the
+    serialised tests' bar, 2e-4 of the row's largest value): targets share
+    slots, words leave the window and come back after their slot would have
+    expired, and sentences end in the middle of a batch of targets."""
+    V = 150
+    corpus = inputs.zipf_ids(4_003, V, 1.0, 9)
+    table, _ = oracle.build_tables(inputs.word_counts(corpus, V), 0.75, 0.0, 10**5,
+                                   want_thresh=False)
+    kw = dict(window=window, K=K, sentence_len=129, seed=3)
+    M_in = inputs.init_matrix(V, D, "uniform", 2)
+    M_out = inputs.init_matrix(V, D, "zeros", 0)
+    oi, oo = M_in.copy(), M_out.copy()
+    oracle.train_epoch(oracle.Sampling(corpus, table, None, **kw), oi, oo)
+    gi, go = to_dev(M_in), to_dev(M_out)
+    w2v.train_epoch(to_dev(corpus), gi, go, to_dev(table), None, max_inflight=1,
+                    hot_rows=5, split_rows=2, **kw)
+    for g, o in ((gi, oi), (go, oo)):
+        d = np.abs(g.cpu().numpy().astype(np.float64) - o)
+        scale = np.abs(o).max(axis=1, keepdims=True) + 1e-3 * np.abs(o).max()
+        assert float((d / scale).max()) < 2e-4
