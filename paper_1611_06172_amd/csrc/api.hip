@@ -610,6 +610,78 @@ int w2v_debug_minibatches(const int32_t* corpus, int64_t T, int64_t pos_begin,
   return ok();
 }
 
+}  // extern "C"
+
+namespace w2v {
+
+static SortedStepArgs sorted_args(int32_t B, int32_t N, int32_t K, const int32_t* targets,
+                                  const int32_t* contexts, const int32_t* negatives,
+                                  const float* alpha, float alpha_scalar, float* M_in,
+                                  float* M_out, int32_t V, int32_t D, int32_t ld,
+                                  int64_t* stats, int32_t* status) {
+  SortedStepArgs a{};
+  a.status = status;
+  a.B = B;
+  a.N = N;
+  a.K = K;
+  a.targets = targets;
+  a.contexts = contexts;
+  a.negatives = negatives;
+  a.alpha = alpha;
+  a.alpha_scalar = alpha_scalar;
+  a.M_in = M_in;
+  a.M_out = M_out;
+  a.V = V;
+  a.D = D;
+  a.ld = ld;
+  a.stats = stats;
+  return a;
+}
+
+// How w2v_step_batch sums the updates of a row, all three in fp64 with one
+// rounding per element.
+enum class StepRoute {
+  kAtomic,  // fp64 atomics into V x ld delta buffers, cleared and applied whole
+  kStaged,  // the sorted batch: staging rows, summed per row
+  kPulled,  // the same without staging rows: errors kept, updates formed again
+};
+
+// The fastest route that the workspace (two fp64 V x ld buffers) allows, by
+// estimates fitted to one MI355X (us measured / estimated at B, N, K, V, D):
+//   atomic  clearing and applying 4 V ld fp64 values at 4.8 TB/s, and per
+//           updated row 0.74 ns and 39 ps for each 64-byte atomic request
+//           (eight fp64 values), under Zipf(1.0) ids (65536, 10, 5, 1e5, 300:
+//           2580 / 2550; 65536, 10, 5, 1e5, 100: 1390 / 1400; 4096, 10, 5,
+//           1e4, 300: 184 / 182; 64, 10, 5, 1e5, 300: 235 / 231);
+//   staged  2.8 ps per staged element and 90 us of launches and of the chain
+//           of 64 entries per wavefront (16384, 10, 5, 1e5, 300: 295 / 310;
+//           4096: 124 / 145; 512: 104 / 97);
+//   pulled  2 N (K + 1) partner rows a minibatch at 35 + 0.2 D ps each, at
+//           least 250 us for the chain of a wavefront, and 120 us beside it
+//           (65536, 10, 5, 1e5, 300: 992 / 870; 65536, 10, 25, 1e5, 300:
+//           3180 / 3360; 4096, 10, 5, 1e4, 300: 360 / 370).
+static StepRoute step_route(int32_t B, int32_t N, int32_t K, int32_t V, int32_t D,
+                            int32_t ld, size_t workspace) {
+  const int64_t n = (int64_t)B * ((int64_t)N + K + 1);
+  if (n > INT32_MAX) return StepRoute::kAtomic;
+  const double atomic_us = 15.0 + 32.0 * (double)V * ld / 4.8e6 +
+                           (double)n * (0.74e-3 + 39e-6 * ((D + 7) / 8));
+  const double staged_us = 90.0 + (double)n * D * 2.8e-6;
+  const double rows_us = 2.0 * (double)B * N * (K + 1) * (35e-6 + 0.2e-6 * D);
+  const double pulled_us = 120.0 + (rows_us > 250.0 ? rows_us : 250.0);
+  // a partner per lane: at most 64 output columns
+  const bool pull_ok = K < 64 && pulled_us < atomic_us &&
+                       sorted_step_workspace_bytes(B, N, K, V, ld, true) <= workspace;
+  if (staged_us < atomic_us && (!pull_ok || staged_us < pulled_us) &&
+      sorted_step_workspace_bytes(B, N, K, V, ld, false) <= workspace)
+    return StepRoute::kStaged;
+  return pull_ok ? StepRoute::kPulled : StepRoute::kAtomic;
+}
+
+}  // namespace w2v
+
+extern "C" {
+
 size_t w2v_step_batch_workspace_bytes(int32_t V, int32_t ld) {
   if (V <= 0 || ld <= 0) return 0;
   const size_t one = (size_t)V * (size_t)ld * sizeof(double);
@@ -650,6 +722,15 @@ int w2v_step_batch(int32_t B, int32_t N, int32_t K, const int32_t* targets,
   if (B == 0 || N == 0) return ok();
 
   hipStream_t s = (hipStream_t)stream;
+  const StepRoute route = step_route(B, N, K, V, D, ld, need);
+  if (route != StepRoute::kAtomic) {
+    const SortedStepArgs a = sorted_args(B, N, K, targets, contexts, negatives, alpha,
+                                         alpha_scalar, M_in, M_out, V, D, ld, stats, status);
+    const hipError_t e = launch_step_sorted(C, nmax, a, workspace,
+                                            route == StepRoute::kPulled, s);
+    if (e != hipSuccess) return hip_fail(e, "step kernel launch");
+    return ok();
+  }
 
   StepArgs a{};
   a.status = status;
@@ -678,7 +759,7 @@ int w2v_step_batch(int32_t B, int32_t N, int32_t K, const int32_t* targets,
 size_t w2v_step_batch_sorted_workspace_bytes(int32_t B, int32_t N, int32_t K,
                                              int32_t V, int32_t ld) {
   if (B < 0 || N < 0 || K < 0 || V <= 0 || ld <= 0) return 0;
-  return sorted_step_workspace_bytes(B, N, K, V, ld);
+  return sorted_step_workspace_bytes(B, N, K, V, ld, false);
 }
 
 int w2v_step_batch_sorted(int32_t B, int32_t N, int32_t K, const int32_t* targets,
@@ -716,23 +797,9 @@ int w2v_step_batch_sorted(int32_t B, int32_t N, int32_t K, const int32_t* target
   if (rc != W2V_OK) return rc;
   if (B == 0 || N == 0) return ok();
 
-  SortedStepArgs a{};
-  a.status = status;
-  a.B = B;
-  a.N = N;
-  a.K = K;
-  a.targets = targets;
-  a.contexts = contexts;
-  a.negatives = negatives;
-  a.alpha = alpha;
-  a.alpha_scalar = alpha_scalar;
-  a.M_in = M_in;
-  a.M_out = M_out;
-  a.V = V;
-  a.D = D;
-  a.ld = ld;
-  a.stats = stats;
-  hipError_t e = launch_step_sorted(C, nmax, a, workspace, (hipStream_t)stream);
+  const SortedStepArgs a = sorted_args(B, N, K, targets, contexts, negatives, alpha,
+                                       alpha_scalar, M_in, M_out, V, D, ld, stats, status);
+  hipError_t e = launch_step_sorted(C, nmax, a, workspace, false, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "sorted step launch");
   return ok();
 }

@@ -78,6 +78,7 @@ struct SortedStepArgs {
   int32_t* status;         // NULL or the device's error word (host-mapped)
   float* stage_in;         // [B][N][ld] updates of the distinct input rows
   float* stage_out;        // [B][K+1][ld] updates of the output rows
+  float* errors;           // [B][N][K+1] errors instead of staging rows (pulled)
   uint32_t* key_in;        // [B][N] sort key of each staging row: the M_in
                            // row id, 2V if unused
   int32_t* val_in;         // [B][N] staging index
@@ -103,10 +104,10 @@ hipError_t launch_step(int C, int nmax, const StepArgs& a, int grid,
 bool train_shape_supported(int C, int nmax);
 // Sorted snapshot batch (step_sorted.hip).
 size_t sorted_step_workspace_bytes(int32_t B, int32_t N, int32_t K, int32_t V,
-                                   int32_t ld);
+                                   int32_t ld, bool pull);
 bool sorted_step_supported(int C, int nmax);
 hipError_t launch_step_sorted(int C, int nmax, SortedStepArgs a, void* workspace,
-                              hipStream_t s);
+                              bool pull, hipStream_t s);
 int columns_for(int D);      // compiled C for a row length, 0 if none
 int inputs_cap_for(int n);   // compiled nmax for n input words, 0 if none
 int train_blocks_per_cu(int C, int nmax, int K);

@@ -608,6 +608,25 @@ struct Core {
     }
   }
 
+  // The errors alone: io.put_errors(k0, T, e) gets those of the block at
+  // column k0 and input rows 8 T .. 8 T + 7, lane 8 i + k holding slot (i, k).
+  template <class Io>
+  __device__ __forceinline__ void run_errors(Io& io, int lane, const Minibatch& mb,
+                                             float alpha) {
+#pragma unroll 1
+    for (int k0 = 0; k0 < (kMulti ? mb.n_out : 1); k0 += KB) {
+      float e[kTiles], et[kTiles], no_loss = 0.f;
+      errors_of<0>(mb, lane, k0, alpha, false, no_loss, e, et);
+#pragma unroll
+      for (int t = 0; t < kTiles; ++t)
+        if (8 * t < mb.n) io.put_errors(mb, k0, t, k0 + KB < mb.n_out ? KB : mb.n_out - k0,
+                                        e[t]);
+      if constexpr (kMulti) {
+        if (k0 + KB < mb.n_out) load_block(io, mb, k0 + KB, o);
+      }
+    }
+  }
+
   static __device__ __forceinline__ float lane_of(float x, int l) {
     return __int_as_float(__builtin_amdgcn_ds_bpermute((l & 63) * 4, __float_as_int(x)));
   }

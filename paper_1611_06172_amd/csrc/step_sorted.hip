@@ -23,6 +23,18 @@
 //      in span order, and applies the total.
 // Traffic per batch: the gathered rows, one staging row written and read
 // per update, the keys, and one read and write per touched row.
+//
+// Pulled batches (w2v_step_batch, whose workspace does not hold the staging
+// rows of a large batch): k_stage keeps only the errors E (4 N (K + 1) bytes
+// a minibatch), and k_reduce forms an entry's update again from them, E O
+// from the K + 1 output rows or E^T A from the N input rows of its
+// minibatch, in the same order of fused multiply-adds, so to the same bits.
+// The input rows are reduced first, from the unchanged M_out, into rows kept
+// aside (next_in); then the output columns, from the unchanged M_in, into
+// M_out; then k_reduce_copy moves the new input rows into M_in. The partner
+// rows (2 N (K + 1) a minibatch) come from L2 and the memory-side cache:
+// 7.9e6 rows of 1.2 KB take 0.74 ms at the kernel-test configuration, where
+// the 3.8e7 fp64 atomic requests of the delta buffers took 2.34 ms.
 #include <hip/hip_runtime.h>
 
 #include "batch_ids.h"
@@ -41,7 +53,15 @@ struct StageIo {
   const SortedStepArgs& a;
   float* in;
   float* out;
+  float* errors;  // [N][K + 1] of this minibatch (pulled batches)
   int lane;
+
+  // Errors of output columns k0 .. k0 + cols - 1 and input rows from 8 t on.
+  __device__ __forceinline__ void put_errors(const Minibatch& mb, int k0, int t, int cols,
+                                             float e) const {
+    const int i = 8 * t + (lane >> 3), k = lane & 7;
+    if (i < mb.n && k < cols) errors[i * (a.K + 1) + k0 + k] = e;
+  }
 
   __device__ __forceinline__ void load_in(int id, bool ok, float (&r)[C]) const {
     load_row<C, false>(a.M_in, id, a.ld, ok ? a.D : 0, lane, r);
@@ -77,7 +97,7 @@ struct StageIo {
   }
 };
 
-template <int C, int NMAX, bool kMulti>
+template <int C, int NMAX, bool kMulti, bool kPull>
 __global__ __launch_bounds__(kWave) void k_stage(SortedStepArgs a) {
   const int lane = threadIdx.x;
   const int n_slots_out = a.K + 1;
@@ -90,7 +110,8 @@ __global__ __launch_bounds__(kWave) void k_stage(SortedStepArgs a) {
     const Minibatch mb = stage_minibatch<(NMAX > 16)>(lane, ids.ctx, ids.present,
                                                       ids.target, ids.neg, a.K);
     const int64_t in0 = b * a.N, out0 = b * n_slots_out;
-    StageIo<C> io{a, a.stage_in + in0 * a.ld, a.stage_out + out0 * a.ld, lane};
+    StageIo<C> io{a, a.stage_in + in0 * a.ld, a.stage_out + out0 * a.ld,
+                  a.errors + in0 * n_slots_out, lane};
     Core<C, NMAX, kMulti> core;
     if (use) core.load(io, mb);
     // Keys of this minibatch's staging rows (2V where nothing is staged).
@@ -115,9 +136,12 @@ __global__ __launch_bounds__(kWave) void k_stage(SortedStepArgs a) {
       ++applied;
       sum_n += n;
       rows += mb.n + mb.n_out;
+      const float alpha = a.alpha != nullptr ? a.alpha[b] : a.alpha_scalar;
       float no_loss = 0.f;
-      core.run(io, lane, mb, a.alpha != nullptr ? a.alpha[b] : a.alpha_scalar, false,
-               no_loss);
+      if constexpr (kPull)
+        core.run_errors(io, lane, mb, alpha);
+      else
+        core.run(io, lane, mb, alpha, false, no_loss);
     }
   }
   if (lane == 0) report_bad_ids(a.status, rejected);
@@ -141,7 +165,21 @@ struct ReduceArgs {
   double* pieces;          // [2 n_chunks][pstride], pstride >= 64 C
   int32_t V, D;
   int64_t ld, pstride;
+  uint32_t key_lo, key_hi; // k_reduce handles the keys in [key_lo, key_hi)
+  float* W_in;             // where new M_in rows go: M_in, or (pulled) next_in
+  // pulled batches: the errors and ids of the minibatches
+  const float* errors;     // [B][N][K + 1]
+  const uint32_t* ids_in;  // [B][N], [B][K + 1]: the sort keys as staged
+  const uint32_t* ids_out;
+  int32_t N, K;
+  int32_t out_base;        // entries from here on are output columns
 };
+
+// Where the new values of a sort key's row go (keys < 2V).
+__device__ __forceinline__ float* key_row_out(const ReduceArgs& r, uint32_t key) {
+  return key < (uint32_t)r.V ? r.W_in + (int64_t)key * r.ld
+                             : r.M_out + (int64_t)(key - (uint32_t)r.V) * r.ld;
+}
 
 // Matrix row a sort key names (keys < 2V).
 __device__ __forceinline__ float* key_row(const ReduceArgs& r, uint32_t key) {
@@ -149,17 +187,27 @@ __device__ __forceinline__ float* key_row(const ReduceArgs& r, uint32_t key) {
                              : r.M_out + (int64_t)(key - (uint32_t)r.V) * r.ld;
 }
 
+// The row of `key`, whose values were m, becomes fp32(m + sum) where the sum
+// is not 0.
 template <int C>
-__device__ __forceinline__ void apply_sum(const ReduceArgs& r, uint32_t key,
-                                          int lane, const double (&sum)[C]) {
-  float* row = key_row(r, key);
-  float m[C];
-  load_row<C, false>(row, 0, r.ld, r.D, lane, m);
+__device__ __forceinline__ void store_sum(const ReduceArgs& r, uint32_t key, int lane,
+                                          const float (&m)[C], const double (&sum)[C]) {
+  float* row = key_row_out(r, key);
+  const bool in_place = r.W_in == r.M_in;
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     const int col = lane + kWave * c;
-    if (col < r.D && sum[c] != 0.0) row[col] = (float)((double)m[c] + sum[c]);
+    if (col < r.D && (sum[c] != 0.0 || !in_place))
+      row[col] = sum[c] != 0.0 ? (float)((double)m[c] + sum[c]) : m[c];
   }
+}
+
+template <int C>
+__device__ __forceinline__ void apply_sum(const ReduceArgs& r, uint32_t key,
+                                          int lane, const double (&sum)[C]) {
+  float m[C];
+  load_row<C, false>(key_row(r, key), 0, r.ld, r.D, lane, m);
+  store_sum<C>(r, key, lane, m, sum);
 }
 
 // Piece rows hold all 64 C columns (zero past D), so they are written and
@@ -186,8 +234,32 @@ __device__ __forceinline__ void load_masked(const float* p, int n_bytes, int lan
         __builtin_amdgcn_raw_buffer_load_b32(rs, (lane + kWave * c) * 4, 0, 0));
 }
 
-template <int C>
+// Where k_reduce finds the update of a sorted entry. kPull: no staging rows;
+// the update of an input row is formed again from its minibatch's errors and
+// output rows, that of an output column from the errors and input rows, in
+// the staged kernel's order of fused multiply-adds, so to the same bits.
+//
+// Ids (sort keys) and errors of the partners of slot `slot` of minibatch b,
+// one per lane; 2V where there is none.
+__device__ __forceinline__ void load_partners(const ReduceArgs& r, int b, int slot,
+                                              bool is_in, bool valid, int lane,
+                                              uint32_t& key, float& error) {
+  const int n_out = r.K + 1;
+  const int most = !valid ? 0 : is_in ? n_out : r.N;
+  key = 2u * (uint32_t)r.V;
+  error = 0.f;
+  if (lane < most) {
+    const int64_t in0 = (int64_t)b * r.N;
+    key = is_in ? r.ids_out[(int64_t)b * n_out + lane] : r.ids_in[in0 + lane];
+    const int i = is_in ? slot : lane, k = is_in ? lane : slot;
+    error = r.errors[(in0 + i) * n_out + k];
+  }
+}
+
+template <int C, bool kPull>
 __global__ __launch_bounds__(kWave) void k_reduce(ReduceArgs r) {
+  constexpr int kBatch = kPull ? 4 : w2v::kBatch;
+  constexpr int kRows = 4;  // partner rows in flight
   const int lane = threadIdx.x;
   const int64_t n_chunks = (r.n + kChunk - 1) / kChunk;
   static_assert(kChunk == kWave, "one sorted entry per lane");
@@ -197,6 +269,19 @@ __global__ __launch_bounds__(kWave) void k_reduce(ReduceArgs r) {
     // The chunk's keys and staging indices, one per lane.
     const uint32_t kl = lane < cnt ? r.key[lo + lane] : 0xffffffffu;
     const int32_t vl = lane < cnt ? r.val[lo + lane] : 0;
+    // The minibatch and the slot within it of this lane's entry.
+    int eb = 0, es = 0;
+    const bool e_in = vl < r.out_base;
+    if constexpr (kPull) {
+      const uint32_t idx = (uint32_t)(e_in ? vl : vl - r.out_base);
+      const uint32_t per = (uint32_t)(e_in ? r.N : r.K + 1);
+      eb = (int)(idx / per);
+      es = (int)(idx - (uint32_t)eb * per);
+    }
+    const uint64_t inputs = __ballot(e_in);
+    // Sorted keys: those below key_lo come first.
+    const int j_lo = __popcll(__ballot(lane < cnt && kl < r.key_lo));
+    if (j_lo == cnt || (uint32_t)__builtin_amdgcn_readlane((int)kl, j_lo & 63) >= r.key_hi) continue;
     const uint32_t prev = lo > 0 ? r.key[lo - 1] : 0xffffffffu;
     const uint32_t next = lo + cnt < r.n ? r.key[lo + cnt] : 0xffffffffu;
     uint32_t cur = 0xffffffffu;  // key of the open run (none yet)
@@ -216,37 +301,68 @@ __global__ __launch_bounds__(kWave) void k_reduce(ReduceArgs r) {
       } else if (e == cnt && next == k) {
         put_piece<C>(r, ch, 1, lane, sum);
       } else {
-        float* row = key_row(r, k);
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-          const int col = lane + kWave * c;
-          if (col < r.D && sum[c] != 0.0) row[col] = (float)((double)mrow[c] + sum[c]);
-        }
+        store_sum<C>(r, k, lane, mrow, sum);
       }
     };
     bool done = false;
-    for (int j0 = 0; j0 < cnt && !done; j0 += kBatch) {
+    for (int j0 = j_lo; j0 < cnt && !done; j0 += kBatch) {
       // Issue a batch of staging-row loads, and the matrix row of every run
       // that opens in the batch, then add them in order. A run's matrix row
       // is written by no one else before this wavefront applies it.
       float x[kBatch][C], m[kBatch][C];
+      uint32_t pk[kPull ? kBatch : 1];
+      float pe[kPull ? kBatch : 1];
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const int j = j0 + u;
-        const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)kl, j);
+        const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)kl, j & 63);
         const uint32_t kp = j == 0 ? prev : (uint32_t)__builtin_amdgcn_readlane((int)kl, j - 1);
-        const bool valid = j < cnt && k < 2u * (uint32_t)r.V;
-        const int32_t v = __builtin_amdgcn_readlane(vl, j);
-        load_masked<C>(r.stage + (int64_t)(valid ? v : 0) * r.ld, valid ? r.D * 4 : 0,
-                       lane, x[u]);
+        const bool valid = j < cnt && k < r.key_hi;
+        const int32_t v = __builtin_amdgcn_readlane(vl, j & 63);
+        if constexpr (kPull) {
+          load_partners(r, __builtin_amdgcn_readlane(eb, j & 63), __builtin_amdgcn_readlane(es, j & 63),
+                        ((inputs >> (j & 63)) & 1ull) != 0ull, valid, lane, pk[u], pe[u]);
+        } else {
+          load_masked<C>(r.stage + (int64_t)(valid ? v : 0) * r.ld, valid ? r.D * 4 : 0,
+                         lane, x[u]);
+        }
         const bool opens = valid && k != kp;
         load_masked<C>(key_row(r, opens ? k : 0u), opens ? r.D * 4 : 0, lane, m[u]);
+      }
+      if constexpr (kPull) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          const int j = j0 + u;
+          const bool is_in = ((inputs >> (j & 63)) & 1ull) != 0ull;
+          const float* M = is_in ? r.M_out : r.M_in;
+          // Partners are distinct rows first, unused slots after them.
+          const int count = __popcll(__ballot(pk[u] < 2u * (uint32_t)r.V));
+          const int row = (int)(pk[u] - (is_in ? (uint32_t)r.V : 0u));
+#pragma unroll
+          for (int c = 0; c < C; ++c) x[u][c] = 0.f;
+#pragma unroll 1
+          for (int p0 = 0; p0 < count; p0 += kRows) {
+            float y[kRows][C];
+#pragma unroll
+            for (int p = 0; p < kRows; ++p)
+              load_masked<C>(row_at(M, __builtin_amdgcn_readlane(row, p0 + p), r.ld),
+                             p0 + p < count ? r.D * 4 : 0, lane, y[p]);
+#pragma unroll
+            for (int p = 0; p < kRows; ++p) {
+              if (p0 + p < count) {
+                const float e = lane_value(pe[u], p0 + p);
+#pragma unroll
+                for (int c = 0; c < C; ++c) x[u][c] = fmaf(e, y[p][c], x[u][c]);
+              }
+            }
+          }
+        }
       }
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const int j = j0 + u;
-        const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)kl, j);
-        if (done || j >= cnt || k >= 2u * (uint32_t)r.V) {
+        const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)kl, j & 63);
+        if (done || j >= cnt || k >= r.key_hi) {
           if (!done) end = j;
           done = true;
         } else {
@@ -393,6 +509,42 @@ __global__ __launch_bounds__(kWave) void k_reduce_cross(ReduceArgs r) {
   }
 }
 
+// Pulled batches: the new M_in rows, kept aside while M_in was still read,
+// go into the matrix (one wavefront per 64 sorted entries; the entries that
+// open a run copy its row).
+template <int C>
+__global__ __launch_bounds__(kWave) void k_reduce_copy(ReduceArgs r) {
+  constexpr int kRows = 4;  // rows in flight
+  const int lane = threadIdx.x;
+  const int64_t n_chunks = (r.n + kChunk - 1) / kChunk;
+  for (int64_t ch = blockIdx.x; ch < n_chunks; ch += gridDim.x) {
+    const int64_t e = ch * kChunk + lane;
+    const uint32_t k = e < r.n ? r.key[e] : 0xffffffffu;
+    const uint32_t before = e > 0 && e < r.n ? r.key[e - 1] : 0xffffffffu;
+    uint64_t open = __ballot(k < (uint32_t)r.V && k != before);
+    while (open != 0ull) {
+      int row[kRows], bytes[kRows];
+      float x[kRows][C];
+#pragma unroll
+      for (int u = 0; u < kRows; ++u) {
+        const int l = open != 0ull ? __builtin_ctzll(open) : 0;
+        row[u] = __builtin_amdgcn_readlane((int)k, l);
+        bytes[u] = open != 0ull ? r.D * 4 : 0;
+        open &= open - 1ull;
+        load_masked<C>(row_at(r.W_in, row[u], r.ld), bytes[u], lane, x[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < kRows; ++u) {
+        const __amdgpu_buffer_rsrc_t rs = row_rsrc(row_at(r.M_in, row[u], r.ld), bytes[u]);
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[u][c]), rs,
+                                                (lane + kWave * c) * 4, 0, 0);
+      }
+    }
+  }
+}
+
 #define W2V_SORTED_SHAPES(X) \
   X(1, 10) X(2, 10) X(3, 10) X(4, 10) X(5, 10) X(6, 10) X(8, 10) X(10, 10) \
   X(1, 16) X(2, 16) X(3, 16) X(4, 16) X(5, 16) X(1, 32) X(2, 32)
@@ -400,21 +552,23 @@ __global__ __launch_bounds__(kWave) void k_reduce_cross(ReduceArgs r) {
 using StageKernel = void (*)(SortedStepArgs);
 using ReduceKernel = void (*)(ReduceArgs);
 
-static StageKernel stage_kernel_for(int C, int nmax, int K) {
+static StageKernel stage_kernel_for(int C, int nmax, int K, bool pull) {
   const bool multi = K + 1 > Core<1, 10, false>::KB;
 #define W2V_PICK(c, n) \
-  if (C == c && nmax == n) return multi ? k_stage<c, n, true> : k_stage<c, n, false>;
+  if (C == c && nmax == n)                                                     \
+    return pull ? (multi ? k_stage<c, n, true, true> : k_stage<c, n, false, true>) \
+                : (multi ? k_stage<c, n, true, false> : k_stage<c, n, false, false>);
   W2V_SORTED_SHAPES(W2V_PICK)
 #undef W2V_PICK
   return nullptr;
 }
 
-static bool reduce_kernels_for(int C, ReduceKernel& red, ReduceKernel& spans,
-                               ReduceKernel& cross) {
+static bool reduce_kernels_for(int C, bool pull, ReduceKernel& red, ReduceKernel& spans,
+                               ReduceKernel& cross, ReduceKernel& copy) {
   switch (C) {
 #define W2V_CASE(c) \
   case c:           \
-    red = k_reduce<c>; spans = k_reduce_spans<c>; cross = k_reduce_cross<c>; return true;
+    red = pull ? k_reduce<c, true> : k_reduce<c, false>; spans = k_reduce_spans<c>; cross = k_reduce_cross<c>; copy = k_reduce_copy<c>; return true;
     W2V_CASE(1) W2V_CASE(2) W2V_CASE(3) W2V_CASE(4) W2V_CASE(5) W2V_CASE(6)
     W2V_CASE(8) W2V_CASE(10)
 #undef W2V_CASE
@@ -429,60 +583,54 @@ static int key_bits(int32_t V) {
   return 32 - __builtin_clz(2u * (unsigned)V);  // keys are 0..2V
 }
 
-// Temporary bytes of the sort of n pairs.
-static bool sort_temp_bytes(int64_t n, int32_t V, size_t& bytes) {
-  (void)V;
-  bytes = radix_sort_temp_bytes(n, sizeof(uint32_t));
-  return true;
-}
-
 // Doubles per piece row: at least 64 C for the C a row stride of ld can
 // need (D <= ld; C = ceil(D/64) rounded up to a compiled size, at most one
 // more).
 static int64_t piece_stride(int32_t ld) { return (int64_t)kWave * ((ld + kWave - 1) / kWave + 1); }
 
-// Workspace: staging rows (inputs, then outputs), keys, sorted keys,
-// values, sorted values, pieces, sort temporaries.
+// Workspace: staging rows (inputs, then outputs) or, for a pulled batch, the
+// errors; then keys, sorted keys, values, sorted values, pieces, sort
+// temporaries and, for a pulled batch, the new M_in rows (row r of V).
 struct SortedLayout {
   int64_t n_in, n;
-  size_t stage, ints, pieces, temp, total;
-  bool ok;
+  size_t stage, ints, pieces, temp, next_in, total;
 };
 
 static SortedLayout sorted_layout(int32_t B, int32_t N, int32_t K, int32_t V,
-                                  int32_t ld) {
+                                  int32_t ld, bool pull) {
   SortedLayout L{};
   L.n_in = (int64_t)B * N;
   L.n = L.n_in + (int64_t)B * (K + 1);
-  L.stage = align256(sizeof(float) * (size_t)L.n * ld);
+  L.stage = align256(sizeof(float) * (pull ? (size_t)L.n_in * (size_t)(K + 1)
+                                           : (size_t)L.n * (size_t)ld));
   L.ints = align256(sizeof(uint32_t) * (size_t)L.n);
   L.pieces = align256(sizeof(double) * 2 * (size_t)((L.n + kChunk - 1) / kChunk) *
                      (size_t)piece_stride(ld));
-  size_t t = 0;
-  L.ok = sort_temp_bytes(L.n, V, t);
-  L.temp = align256(t);
-  L.total = L.stage + 4 * L.ints + L.pieces + L.temp;
+  L.temp = align256(radix_sort_temp_bytes(L.n, sizeof(uint32_t)));
+  L.next_in = pull ? align256(sizeof(float) * (size_t)V * (size_t)ld) : 0;
+  L.total = L.stage + 4 * L.ints + L.pieces + L.temp + L.next_in;
   if (L.total == 0) L.total = 256;
   return L;
 }
 
 size_t sorted_step_workspace_bytes(int32_t B, int32_t N, int32_t K, int32_t V,
-                                   int32_t ld) {
-  const SortedLayout L = sorted_layout(B, N, K, V, ld);
-  return L.ok ? L.total : 0;
+                                   int32_t ld, bool pull) {
+  return sorted_layout(B, N, K, V, ld, pull).total;
 }
 
 bool sorted_step_supported(int C, int nmax) {
-  ReduceKernel r, sp, x;
-  return stage_kernel_for(C, nmax, 0) != nullptr && reduce_kernels_for(C, r, sp, x);
+  ReduceKernel r, sp, x, cp;
+  return stage_kernel_for(C, nmax, 0, false) != nullptr &&
+         reduce_kernels_for(C, false, r, sp, x, cp);
 }
 
 hipError_t launch_step_sorted(int C, int nmax, SortedStepArgs a, void* workspace,
-                              hipStream_t s) {
-  StageKernel k = stage_kernel_for(C, nmax, a.K);
-  ReduceKernel red, spans, cross;
-  if (k == nullptr || !reduce_kernels_for(C, red, spans, cross)) return hipErrorInvalidValue;
-  const SortedLayout L = sorted_layout(a.B, a.N, a.K, a.V, (int32_t)a.ld);
+                              bool pull, hipStream_t s) {
+  StageKernel k = stage_kernel_for(C, nmax, a.K, pull);
+  ReduceKernel red, spans, cross, copy;
+  if (k == nullptr || !reduce_kernels_for(C, pull, red, spans, cross, copy))
+    return hipErrorInvalidValue;
+  const SortedLayout L = sorted_layout(a.B, a.N, a.K, a.V, (int32_t)a.ld, pull);
   char* w = (char*)workspace;
   float* stage = (float*)w;
   uint32_t* keys = (uint32_t*)(w + L.stage);
@@ -492,7 +640,8 @@ hipError_t launch_step_sorted(int C, int nmax, SortedStepArgs a, void* workspace
   double* pieces = (double*)(w + L.stage + 4 * L.ints);
   void* temp = (void*)(w + L.stage + 4 * L.ints + L.pieces);
   a.stage_in = stage;
-  a.stage_out = stage + L.n_in * a.ld;
+  a.stage_out = pull ? stage : stage + L.n_in * a.ld;
+  a.errors = stage;
   a.key_in = keys;
   a.val_in = vals;
   a.key_out = keys + L.n_in;
@@ -505,14 +654,26 @@ hipError_t launch_step_sorted(int C, int nmax, SortedStepArgs a, void* workspace
   e = radix_sort_pairs((const uint32_t*)keys, (const int32_t*)vals, keys_sorted,
                        vals_sorted, L.n, key_bits(a.V), temp, s);
   if (e != hipSuccess) return e;
+  float* next_in = (float*)((char*)temp + L.temp);
   ReduceArgs r{keys_sorted, vals_sorted, L.n, stage, a.M_in, a.M_out, pieces,
-               a.V, a.D, a.ld, piece_stride((int32_t)a.ld)};
+               a.V, a.D, a.ld, piece_stride((int32_t)a.ld),
+               0u, 2u * (uint32_t)a.V, pull ? next_in : a.M_in,
+               stage, keys, keys + L.n_in, a.N, a.K, (int32_t)L.n_in};
   if (r.pstride < (int64_t)kWave * C) return hipErrorInvalidValue;
   const int64_t n_chunks = (L.n + kChunk - 1) / kChunk;
   const int rgrid = (int)(n_chunks < 65536 ? n_chunks : 65536);
+  if (pull) {
+    // Input rows first, into next_in: they read M_out as it was. Then the
+    // output columns, which read M_in as it was and move M_out.
+    r.key_hi = (uint32_t)a.V;
+    hipLaunchKernelGGL(red, dim3(rgrid), dim3(kWave), 0, s, r);
+    r.key_lo = (uint32_t)a.V;
+    r.key_hi = 2u * (uint32_t)a.V;
+  }
   hipLaunchKernelGGL(red, dim3(rgrid), dim3(kWave), 0, s, r);
   hipLaunchKernelGGL(spans, dim3(rgrid), dim3(kWave), 0, s, r);
   hipLaunchKernelGGL(cross, dim3(rgrid), dim3(kWave), 0, s, r);
+  if (pull) hipLaunchKernelGGL(copy, dim3(rgrid), dim3(kWave), 0, s, r);
   return hipGetLastError();
 }
 
