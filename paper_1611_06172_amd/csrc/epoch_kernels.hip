@@ -39,6 +39,7 @@ namespace w2v {
 // pending updates of this word, which the read adds and to which this
 // minibatch's update is added. A lane reads and writes its own columns only.
 constexpr int kSlotHeld = 64;
+constexpr int kMaxPendingSlots = 16;
 
 // Smallest value of lanes 0..15 (x of the other lanes is not used).
 __device__ __forceinline__ int row0_min(int x) {
@@ -73,20 +74,27 @@ struct PendingSlots {
   __device__ __forceinline__ int find(const Minibatch& mb, int q, int lane) {
     int code = -1;
     miss = __ballot(lane < mb.n && mb.in_id >= from);
-#pragma unroll
-    for (int i = 0; i < NMAX; ++i) {
-      if (i < mb.n && ((miss >> i) & 1ull) != 0ull) {
-        const uint64_t held = __ballot(lane < count &&
-                                       id == __builtin_amdgcn_readlane(mb.in_id, i));
-        if (held != 0ull) {
-          const int s = __builtin_ctzll(held);
-          if (lane == i) code = kSlotHeld + s;
-          if (lane == s) used = q;
-          miss &= ~(1ull << i);
-        }
+    if (miss == 0ull) return code;
+    uint64_t hit = 0ull;
+    find_from<0, NMAX>(mb, code, hit);
+    miss &= ~__ballot(code >= 0);
+    if (((hit >> lane) & 1ull) != 0ull) used = q;
+    return code;
+  }
+  // Inputs I, I + 1, ... (free slots and the lanes past the slots hold -1,
+  // which no word is).
+  template <int I, int NMAX>
+  __device__ __forceinline__ void find_from(const Minibatch& mb, int& code,
+                                            uint64_t& hit) const {
+    if constexpr (I < NMAX) {
+      if (I < mb.n) {
+        const uint64_t held = __ballot(id == __builtin_amdgcn_readlane(mb.in_id, I));
+        const int c = held != 0ull ? kSlotHeld + __builtin_ctzll(held) : -1;
+        code = (int)threadIdx.x == I ? c : code;
+        hit |= held;
+        find_from<I + 1, NMAX>(mb, code, hit);
       }
     }
-    return code;
   }
 
   // Expires slots and gives slots to the words that have none.
@@ -652,8 +660,6 @@ static size_t epoch_dyn_lds(const EpochArgs& a) {
 }
 
 static size_t slot_bytes(int C) { return sizeof(float) * (size_t)kWave * C; }
-
-constexpr int kMaxPendingSlots = 16;
 
 // Shape of the training launch for (C, nmax, K) on the current device:
 // targets formed at once, pending slots and resident workgroups per CU.

@@ -387,6 +387,29 @@ __device__ __forceinline__ float reduce_tile(const F& value, int lane) {
   }
 }
 
+// 1 / x for x in [1, 4], within one ulp: the hardware's reciprocal and one
+// Newton step.
+__device__ __forceinline__ float recip_near1(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(r, fmaf(-x, r, 1.f), r);
+}
+
+// log(1 + t) for t in [0, 1], within about an ulp: 2 atanh(s), s = t / (2 +
+// t) <= 1/3, by its series up to s^15 (the next term is below 2e-9 of the
+// sum).
+__device__ __forceinline__ float log1p_unit(float t) {
+  const float s = t * recip_near1(2.f + t);
+  const float q = s * s;
+  float p = 1.f / 15.f;
+  p = fmaf(p, q, 1.f / 13.f);
+  p = fmaf(p, q, 1.f / 11.f);
+  p = fmaf(p, q, 1.f / 9.f);
+  p = fmaf(p, q, 1.f / 7.f);
+  p = fmaf(p, q, 1.f / 5.f);
+  p = fmaf(p, q, 1.f / 3.f);
+  return fmaf(2.f * s * q, p, 2.f * s);
+}
+
 // Error and loss of one slot of a minibatch of one target: column 0 is the
 // target (label 1), the others negatives (label 0); both scaled by the row
 // and column multiplicities (wgt).
@@ -394,10 +417,15 @@ __device__ __forceinline__ float target_error(bool is_target, float x, float wgt
                                               float alpha, bool want_loss,
                                               float& loss_part) {
   // label - sigma(x) is sigma(-x) for the target and -sigma(x) for a
-  // negative; evaluating sigma(z) directly avoids cancelling against 1.
+  // negative; evaluating sigma(z) directly avoids cancelling against 1. With
+  // t = e^-|z| it is 1 / (1 + t), or t / (1 + t) where z < 0, and the loss
+  // is max(z, 0) + log(1 + t): one exponential, no divide and no library
+  // logarithm (a wavefront on its own spent a quarter of a minibatch here).
   const float z = is_target ? -x : x;
-  const float sz = 1.f / (1.f + __expf(-z));
-  if (want_loss) loss_part += wgt * softplus(z);
+  const float t = __expf(-fabsf(z));
+  const float r = recip_near1(1.f + t);
+  const float sz = z < 0.f ? t * r : r;
+  if (want_loss) loss_part += wgt * (fmaxf(z, 0.f) + log1p_unit(t));
   return wgt * alpha * (is_target ? sz : -sz);
 }
 
