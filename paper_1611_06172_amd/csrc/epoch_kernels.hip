@@ -746,7 +746,11 @@ bool grouped_shape_supported(int C, int omax) {
 int grouped_blocks_per_cu(int C, int omax, int K) {
   EpochKernel k = grouped_kernel_for(C, omax);
   if (k == nullptr) return 0;
-  return resident_blocks_per_cu(reinterpret_cast<const void*>(k), negatives_lds(K));
+  // No more sentences at once than 160 KB of LDS hold at 11320 bytes and the
+  // negatives each: the concurrency is part of what a launch computes.
+  const size_t per = (11320 + negatives_lds(K) + kLdsGranule - 1) / kLdsGranule * kLdsGranule;
+  return std::min(resident_blocks_per_cu(reinterpret_cast<const void*>(k), negatives_lds(K)),
+                  (int)(kLdsPerCu / per));
 }
 
 hipError_t launch_grouped(int C, int omax, const EpochArgs& a, int grid,

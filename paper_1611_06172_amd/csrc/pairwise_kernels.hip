@@ -11,16 +11,20 @@
 // pair, and the M_in row of i moves once, after its K+1 pairs, by the sum of
 // alpha * error * (M_out row as used).
 //
-// One wavefront per sentence. Per input word, up to kPairBlock output rows
+// One wavefront per sentence. A target's private negatives are drawn for all
+// of its input words at once. Per input word, up to kPairBlock output rows
 // are gathered at once; since the M_in row is fixed during its K+1 pairs,
 // all their inner products come from one transposing reduction, together
-// with |a|^2. A later pair on a row already moved in the same block (a
+// with |a|^2, and where no row is there twice the errors are evaluated one
+// per lane. A later pair on a row already moved in the same block (a
 // repeated negative) then sees x + (sum of earlier errors) |a|^2 and the
 // row moved by those errors, exactly as if it had been re-read. Blocks and
 // input words are processed in order; each gathers its rows after the
 // previous one's writes were issued, so it reads them back moved. Update
 // path as in HogBatch: fp32 atomics for ids < hot_rows, write-through
 // stores otherwise.
+#include <algorithm>
+
 #include "kernel_args.h"
 #include "sentence.h"
 #include "sgns_core.h"
@@ -50,8 +54,7 @@ __device__ __forceinline__ void write_row(float* M, int id, int64_t ld, int D,
 template <int C>
 __global__ __launch_bounds__(kWave) void k_epoch_pairwise(EpochArgs a) {
   __shared__ SentenceLds sl;
-  __shared__ TargetBatch tb;
-  extern __shared__ int32_t negs_lds[];  // [kWave][K], formed and unused
+  extern __shared__ int32_t negs_lds[];  // [input word][K] of the current target
   const int lane = threadIdx.x;
   const int K = a.K;
   const int64_t ld = a.ld;
@@ -70,25 +73,35 @@ __global__ __launch_bounds__(kWave) void k_epoch_pairwise(EpochArgs a) {
     const int n_ret = keep_and_compact<false>(a, sb, len, lane, sl, rejected);
 
     for (int q0 = 0; q0 < n_ret; q0 += kWave) {
-      form_target_batch(a, sb, q0, n_ret, lane, sl, tb, negs_lds);
-      const int cnt = min(kWave, n_ret - q0);
-      for (int j = 0; j < cnt; ++j) {
-        const int n = uniform_int(tb.n[j]);
-        if (n == 0) continue;
+      // The targets alone: their negatives are drawn per input word below.
+      EpochArgs targets_only = a;
+      targets_only.K = 0;
+      uint64_t unused;
+      const FormedTarget t = form_targets(targets_only, sb, q0, n_ret, lane, sl, negs_lds,
+                                          kWave, unused);
+      for (uint64_t todo = __ballot(t.n > 0); todo != 0ull; todo &= todo - 1ull) {
+        const int j = __builtin_ctzll(todo);
+        const int n = __builtin_amdgcn_readlane(t.n, j);
         const int qj = q0 + j;
         const int64_t p = sb + sl.ret_off[qj];
-        const int target = uniform_int(sl.ret_id[qj]);
-        const int lo = uniform_int(tb.lo[j]);
-        const float alpha = uniform_float(tb.alpha[j]);
-        // Every private negative must be a row: otherwise skip the target.
+        const int target = __builtin_amdgcn_readlane(t.id, j);
+        const int lo = __builtin_amdgcn_readlane(t.lo, j);
+        const float alpha =
+            __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t.alpha), j));
+        // Every input word's negatives at once, one per lane: drawn word by
+        // word, each word began with a Philox block and a random read of the
+        // table. All must be rows: otherwise skip the target.
+        __syncthreads();
         bool bad = false;
         for (int base = 0; base < n * K; base += kWave) {
           const int idx = base + lane;
           if (idx < n * K) {
             const int neg = pair_negative(a, p, idx / K, idx % K);
             bad |= (neg < 0 || neg >= a.V);
+            negs_lds[idx] = neg;
           }
         }
+        __syncthreads();
         if (__ballot(bad) != 0ull) {
           ++rejected;
           continue;
@@ -96,67 +109,73 @@ __global__ __launch_bounds__(kWave) void k_epoch_pairwise(EpochArgs a) {
         ++n_mb;
         sum_n += n;
         rows += (int64_t)n * (K + 2);  // per input word: its row, K + 1 output rows
-        float loss_t = 0.f;  // lane-uniform
+        float loss_t = 0.f;            // every lane's share
 
         for (int i = 0; i < n; ++i) {
           int jj = lo + i;
           if (jj >= qj) ++jj;
           const int cid = uniform_int(sl.ret_id[jj]);
-          const int my_neg = lane < K ? pair_negative(a, p, i, lane) : -1;
           float av[C], temp[C];
           load_row<C, true>(a.M_in, cid, ld, D, lane, av);
 #pragma unroll
           for (int c = 0; c < C; ++c) temp[c] = 0.f;
 
           for (int k0 = 0; k0 <= K; k0 += kPairBlock) {
-            int ids[kPairBlock];
-#pragma unroll
-            for (int kk = 0; kk < kPairBlock; ++kk) {
-              const int col = k0 + kk;
-              int id = -1;
-              if (col == 0) {
-                id = target;
-              } else if (col <= K) {
-                id = __builtin_amdgcn_readlane(my_neg, col - 1);
-                if (id == target) id = -1;  // masked: the pair is skipped
-              }
-              ids[kk] = id;
+            // Lane kk: output word of pair k0 + kk, -1 if there is none or it
+            // is masked (a negative that equals the target).
+            const int col = k0 + lane;
+            int id = -1;
+            if (lane < kPairBlock && col <= K) {
+              id = col == 0 ? target : negs_lds[i * K + col - 1];
+              if (col > 0 && id == target) id = -1;
             }
+            const uint64_t used = __ballot(id >= 0);
+            const bool repeats = has_repeat<false>(id >= 0 ? id : -1 - lane);
             float o[kPairBlock][C];
 #pragma unroll
-            for (int kk = 0; kk < kPairBlock; ++kk) {
-              if (ids[kk] >= 0) {
-                load_row<C, true>(a.M_out, ids[kk], ld, D, lane, o[kk]);
-              } else {
+            for (int kk = 0; kk < kPairBlock; ++kk)
+              load_row<C, true>(a.M_out, __builtin_amdgcn_readlane(id, kk), ld,
+                                ((used >> kk) & 1ull) != 0ull ? D : 0, lane, o[kk]);
+            // Inner products of the block (lane kk) and |a|^2 (lane 8) in one
+            // reduction.
+            const float xs = reduce_tile<2, kPairBlock>(
+                [&](int r, int kk) {
+                  if (r > 0 && kk > 0) return 0.f;
+                  float acc = 0.f;
 #pragma unroll
-                for (int c = 0; c < C; ++c) o[kk][c] = 0.f;
+                  for (int c = 0; c < C; ++c)
+                    acc = fmaf(av[c], r == 0 ? o[kk][c] : av[c], acc);
+                  return acc;
+                },
+                lane);
+            if (!repeats) {
+              // No row twice: the pairs of the block do not see each other,
+              // and lane kk evaluates pair kk.
+              float g_lane = 0.f;
+              if (id >= 0) g_lane = target_error(col == 0, xs, 1.f, alpha, want_loss, loss_t);
+#pragma unroll
+              for (int kk = 0; kk < kPairBlock; ++kk) {
+                if (((used >> kk) & 1ull) == 0ull) continue;
+                const float g = lane_value(g_lane, kk);
+                float d[C];
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                  temp[c] = fmaf(g, o[kk][c], temp[c]);
+                  d[c] = g * av[c];
+                }
+                write_row<C>(a.M_out, __builtin_amdgcn_readlane(id, kk), ld, D, lane,
+                             a.hot_rows, o[kk], d);
               }
+              continue;
             }
-            // Inner products of the block and |a|^2 in one reduction.
-            float v[kWave];
-#pragma unroll
-            for (int kk = 0; kk < kPairBlock; ++kk) {
-              float acc = 0.f;
-#pragma unroll
-              for (int c = 0; c < C; ++c) acc = fmaf(av[c], o[kk][c], acc);
-              v[kk] = acc;
-            }
-            {
-              float acc = 0.f;
-#pragma unroll
-              for (int c = 0; c < C; ++c) acc = fmaf(av[c], av[c], acc);
-              v[kPairBlock] = acc;
-            }
-#pragma unroll
-            for (int t = kPairBlock + 1; t < kWave; ++t) v[t] = 0.f;
-            const float xs = xpose_reduce64(v, lane);
+            // Pairs in order (lane-uniform): g = alpha (label - sigma(x)), x
+            // taken after the earlier pairs of the block on the same row.
             const float aa = lane_value(xs, kPairBlock);
-
-            // Pairs in order (lane-uniform): g = alpha (label - sigma(x)),
-            // x taken after the earlier pairs of the block on the same row.
+            int ids[kPairBlock];
             float g[kPairBlock], before[kPairBlock];
 #pragma unroll
             for (int kk = 0; kk < kPairBlock; ++kk) {
+              ids[kk] = __builtin_amdgcn_readlane(id, kk);
               g[kk] = 0.f;
               before[kk] = 0.f;
               if (ids[kk] < 0) continue;
@@ -164,13 +183,11 @@ __global__ __launch_bounds__(kWave) void k_epoch_pairwise(EpochArgs a) {
 #pragma unroll
               for (int k2 = 0; k2 < kk; ++k2)
                 if (ids[k2] == ids[kk]) prev += g[k2];
-              const float x = lane_value(xs, kk) + prev * aa;
-              const bool is_target = (k0 + kk == 0);
-              const float z = is_target ? -x : x;
-              const float sz = 1.f / (1.f + __expf(-z));
-              g[kk] = alpha * (is_target ? sz : -sz);
+              float loss_pair = 0.f;
+              g[kk] = target_error(k0 + kk == 0, lane_value(xs, kk) + prev * aa, 1.f, alpha,
+                                   want_loss, loss_pair);
               before[kk] = prev;
-              if (want_loss) loss_t += softplus(z);
+              if (lane == 0) loss_t += loss_pair;
             }
             // temp += g * (row as used); each distinct row moves once by the
             // sum of its errors.
@@ -202,15 +219,13 @@ __global__ __launch_bounds__(kWave) void k_epoch_pairwise(EpochArgs a) {
         }
 
         if (want_loss) {
-          const int b = (int)(p * (int64_t)a.n_buckets / a.T);
+          const int b = __builtin_amdgcn_readlane(t.bucket, j);
           if (b != bucket) {
             if (bucket >= 0) flush_loss(a.loss, bucket, lsum, lcnt, lane);
             bucket = b;
           }
-          if (lane == 0) {
-            lsum += (double)loss_t;
-            lcnt += (double)n;
-          }
+          lsum += (double)loss_t;
+          lcnt += (double)n;
         }
       }
       __syncthreads();
@@ -242,7 +257,14 @@ int pairwise_blocks_per_cu(int C, int K) {
   PairKernel k = pairwise_kernel_for(C);
   if (k == nullptr) return 0;
   const size_t dyn = sizeof(int32_t) * kWave * (size_t)(K > 0 ? K : 1);
-  return resident_blocks_per_cu(reinterpret_cast<const void*>(k), dyn);
+  // Sentences at once are part of what a default launch computes (how far it
+  // drifts from the sequential epoch): five waves per SIMD up to D = 128,
+  // four to 320, three to 512, two above, and no more than 160 KB of LDS hold
+  // at 7680 + 256 K bytes each, whatever a build's registers would allow.
+  const int by_rows = 4 * (C <= 2 ? 5 : C <= 5 ? 4 : C <= 8 ? 3 : 2);
+  const int by_lds = (int)((160 * 1024) / ((7680 + dyn + 1279) / 1280 * 1280));
+  const int resident = resident_blocks_per_cu(reinterpret_cast<const void*>(k), dyn);
+  return std::min(resident, std::min(by_rows, by_lds));
 }
 
 hipError_t launch_pairwise(int C, const EpochArgs& a, int grid, hipStream_t s) {
