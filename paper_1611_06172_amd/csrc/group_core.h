@@ -44,8 +44,11 @@ struct GroupError {
                                               int lk, float x,
                                               bool want_loss,
                                               float& loss_part) const {
-    const float sp = 1.f / (1.f + __expf(x));    // sigma(-x)
-    const float sn = 1.f / (1.f + __expf(-x));   // sigma(x)
+    // one exponential: t = e^-|x|, sigma of the smaller side is t / (1 + t)
+    const float t = __expf(-fabsf(x));
+    const float r = recip_near1(1.f + t);
+    const float sp = x < 0.f ? r : t * r;        // sigma(-x)
+    const float sn = x < 0.f ? t * r : r;        // sigma(x)
     const uint32_t tb = gl->tbits[lk];
     const float nw = gl->negw[lk];
     float e = 0.f, l_t = 0.f, l_n = 0.f;
@@ -61,8 +64,9 @@ struct GroupError {
       }
     }
     if (want_loss) {
-      if (l_t != 0.f) loss_part += l_t * softplus(-x);
-      if (l_n != 0.f) loss_part += l_n * softplus(x);
+      const float log_part = log1p_unit(t);
+      if (l_t != 0.f) loss_part += l_t * (fmaxf(-x, 0.f) + log_part);
+      if (l_n != 0.f) loss_part += l_n * (fmaxf(x, 0.f) + log_part);
     }
     return e;
   }

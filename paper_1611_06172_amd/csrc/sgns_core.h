@@ -234,11 +234,6 @@ __device__ __forceinline__ void update_row(float* row, int D, int lane, bool ato
   }
 }
 
-// log(1 + e^z) = -log sigma(-z), without overflow.
-__device__ __forceinline__ float softplus(float z) {
-  return fmaxf(z, 0.f) + log1pf(__expf(-fabsf(z)));
-}
-
 // Row access of a minibatch's live rows by tier: rows id < split_rows of
 // matrix m (0: input, 1: output) have partial rows part[((m split_rows + id)
 // kSplitParts + g) ld], g < kSplitParts, that every read adds and that take
