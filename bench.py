@@ -462,7 +462,8 @@ def kernel_test(args):
         "snapshot": ("no copy of the matrices: every minibatch reads the unchanged "
                      "matrices and its updates go to " +
                      ("staging rows summed in a fixed order" if srt else
-                      "fp64 delta buffers") + ", applied after all minibatches"),
+                      "fp64 sums per row (staged, formed again per row, or "
+                      "delta buffers, by size)") + ", applied after all minibatches"),
     }
     if not args.no_cpu_baseline:
         import oracle

@@ -159,14 +159,7 @@ __device__ __forceinline__ float xpose_tail32(float (&v)[32], int lane) {
   return f_pair_dpp<kDppXor1>(v[0], v[1], b0);
 }
 
-__device__ __forceinline__ float xpose_reduce64(float (&v)[64], int lane) {
-  float w[32];
-#pragma unroll
-  for (int j = 0; j < 32; ++j) w[j] = f_swap_sum32(v[j], v[j + 32]);
-  return xpose_tail32(w, lane);
-}
-
-// The same reduction with value s produced on demand by value(s) (s a
+// Value s is produced on demand by value(s) (s a
 // compile-time index after unrolling), so that values s and s + 32 are
 // formed just before the first step combines them and at most 32 partial
 // sums are live at once.
