@@ -419,6 +419,16 @@ int w2v_step_batch(int32_t B, int32_t N, int32_t K, const int32_t* targets,
                    void* workspace, size_t workspace_bytes, int64_t* stats,
                    void* stream);
 
+/* The route that w2v_step_batch takes for these arguments, for tests of each
+ * route (host only; the matrices are not read). A negative W2V_E* code on
+ * invalid arguments. Matrices that share elements (one matrix passed as both,
+ * overlapping views) take the atomic route. */
+#define W2V_STEP_ROUTE_ATOMIC 0
+#define W2V_STEP_ROUTE_STAGED 1
+#define W2V_STEP_ROUTE_PULLED 2
+int32_t w2v_debug_step_route(int32_t B, int32_t N, int32_t K, const float* M_in,
+                             const float* M_out, int32_t V, int32_t D, int32_t ld);
+
 /* Bytes of workspace w2v_step_batch_sorted needs for B minibatches of N
  * input slots and K negatives over V rows of stride ld (0 on invalid
  * arguments or a failed query): staging rows for every update, sort keys

@@ -638,12 +638,30 @@ static SortedStepArgs sorted_args(int32_t B, int32_t N, int32_t K, const int32_t
   return a;
 }
 
+// Whether an element of one matrix (V rows of D columns, stride ld) is an
+// element of the other: the same matrix passed twice, or views of one buffer
+// that share columns of some rows. The atomic route adds the two matrices'
+// sums one after the other; the others write M_out while the partner rows of
+// M_in are still read, or write a shared row twice, so they need matrices of
+// their own.
+static bool rows_overlap(const float* M_in, const float* M_out, int32_t V, int32_t D,
+                         int32_t ld) {
+  const uint64_t lo = (uint64_t)(uintptr_t)(M_in < M_out ? M_in : M_out);
+  const uint64_t hi = (uint64_t)(uintptr_t)(M_in < M_out ? M_out : M_in);
+  const uint64_t apart = hi - lo, row = 4ull * (uint64_t)ld, used = 4ull * (uint64_t)D;
+  if (apart >= row * (uint64_t)(V - 1) + used) return false;
+  const uint64_t shift = apart % row;  // of the later matrix's rows against the other's
+  if (shift < used) return true;
+  // the later matrix's row reaches into the other's next row, if there is one
+  return shift + used > row && apart / row + 1 < (uint64_t)V;
+}
+
 // How w2v_step_batch sums the updates of a row, all three in fp64 with one
 // rounding per element.
-enum class StepRoute {
-  kAtomic,  // fp64 atomics into V x ld delta buffers, cleared and applied whole
-  kStaged,  // the sorted batch: staging rows, summed per row
-  kPulled,  // the same without staging rows: errors kept, updates formed again
+enum class StepRoute : int32_t {
+  kAtomic = W2V_STEP_ROUTE_ATOMIC,  // fp64 atomics into V x ld delta buffers, cleared and applied whole
+  kStaged = W2V_STEP_ROUTE_STAGED,  // the sorted batch: staging rows, summed per row
+  kPulled = W2V_STEP_ROUTE_PULLED,  // the same without staging rows: errors kept, updates formed again
 };
 
 // The fastest route that the workspace (two fp64 V x ld buffers) allows, by
@@ -660,10 +678,11 @@ enum class StepRoute {
 //           least 250 us for the chain of a wavefront, and 120 us beside it
 //           (65536, 10, 5, 1e5, 300: 992 / 870; 65536, 10, 25, 1e5, 300:
 //           3180 / 3360; 4096, 10, 5, 1e4, 300: 360 / 370).
-static StepRoute step_route(int32_t B, int32_t N, int32_t K, int32_t V, int32_t D,
-                            int32_t ld, size_t workspace) {
+static StepRoute step_route(int32_t B, int32_t N, int32_t K, const float* M_in,
+                            const float* M_out, int32_t V, int32_t D, int32_t ld) {
+  const size_t workspace = w2v_step_batch_workspace_bytes(V, ld);
   const int64_t n = (int64_t)B * ((int64_t)N + K + 1);
-  if (n > INT32_MAX) return StepRoute::kAtomic;
+  if (n > INT32_MAX || rows_overlap(M_in, M_out, V, D, ld)) return StepRoute::kAtomic;
   const double atomic_us = 15.0 + 32.0 * (double)V * ld / 4.8e6 +
                            (double)n * (0.74e-3 + 39e-6 * ((D + 7) / 8));
   const double staged_us = 90.0 + (double)n * D * 2.8e-6;
@@ -681,6 +700,16 @@ static StepRoute step_route(int32_t B, int32_t N, int32_t K, int32_t V, int32_t 
 }  // namespace w2v
 
 extern "C" {
+
+int32_t w2v_debug_step_route(int32_t B, int32_t N, int32_t K, const float* M_in,
+                             const float* M_out, int32_t V, int32_t D, int32_t ld) {
+  if (B < 0 || N < 0 || N > W2V_MAX_BATCH_INPUTS || K < 0 || K > W2V_MAX_NEGATIVE)
+    return fail(W2V_EINVAL, "invalid batch shape");
+  const int rc = check_matrices(M_in, M_out, V, D, ld);
+  if (rc != W2V_OK) return rc;
+  ok();
+  return (int32_t)step_route(B, N, K, M_in, M_out, V, D, ld);
+}
 
 size_t w2v_step_batch_workspace_bytes(int32_t V, int32_t ld) {
   if (V <= 0 || ld <= 0) return 0;
@@ -722,7 +751,7 @@ int w2v_step_batch(int32_t B, int32_t N, int32_t K, const int32_t* targets,
   if (B == 0 || N == 0) return ok();
 
   hipStream_t s = (hipStream_t)stream;
-  const StepRoute route = step_route(B, N, K, V, D, ld, need);
+  const StepRoute route = step_route(B, N, K, M_in, M_out, V, D, ld);
   if (route != StepRoute::kAtomic) {
     const SortedStepArgs a = sorted_args(B, N, K, targets, contexts, negatives, alpha,
                                          alpha_scalar, M_in, M_out, V, D, ld, stats, status);

@@ -92,6 +92,8 @@ def lib():
         _i32, _i32, _i32, _vp, _vp, _vp, _vp, _f32, _vp, _vp, _i32, _i32, _i32,
         _vp, ctypes.c_size_t, _vp, _vp]
     L.w2v_step_batch.restype = ctypes.c_int
+    L.w2v_debug_step_route.argtypes = [_i32, _i32, _i32, _vp, _vp, _i32, _i32, _i32]
+    L.w2v_debug_step_route.restype = ctypes.c_int32
     L.w2v_step_batch_sorted_workspace_bytes.argtypes = [_i32, _i32, _i32, _i32, _i32]
     L.w2v_step_batch_sorted_workspace_bytes.restype = ctypes.c_size_t
     L.w2v_step_batch_sorted.argtypes = L.w2v_step_batch.argtypes
@@ -400,6 +402,19 @@ def alloc_workspace(V: int, ld: int, device="cuda"):
     import torch
     n = step_batch_workspace_bytes(V, ld)
     return torch.empty(n, dtype=torch.uint8, device=device)
+
+
+STEP_ROUTES = {0: "atomic", 1: "staged", 2: "pulled"}
+
+
+def debug_step_route(B: int, N: int, K: int, V: int, D: int, ld: int, *,
+                     in_ptr: int = 1 << 30, out_ptr: int = 1 << 45) -> str:
+    """Route of step_batch (not sorted) for these sizes and the matrices'
+    addresses, which are compared and not read (w2v_debug_step_route)."""
+    r = int(lib().w2v_debug_step_route(B, N, K, in_ptr, out_ptr, V, D, ld))
+    if r < 0:
+        _check(r)
+    return STEP_ROUTES[r]
 
 
 def step_batch_sorted_workspace_bytes(B: int, N: int, K: int, V: int, ld: int) -> int:

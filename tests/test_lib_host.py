@@ -227,3 +227,35 @@ def test_check_loss_rejects():
     assert "n_buckets" in L.w2v_last_error().decode()
     assert L.w2v_check_loss(None, 3, None) == w2v.EINVAL
     assert "NULL" in L.w2v_last_error().decode()
+
+
+@pytest.mark.parametrize("D,ld", [(127, 128), (128, 128), (128, 200), (80, 192)])
+def test_shared_matrices_take_the_atomic_route(D, ld):
+    """w2v_step_batch reads one matrix while it writes the other on every route
+    but the atomic one, so views that share an element must take that one and
+    views that share none need not."""
+    V = 100_000
+    shape = (2_000, 10, 5, V, D, ld)
+    assert w2v.debug_step_route(*shape) != "atomic"
+    base = 1 << 30
+    # row 0 of the later matrix meets the other's rows wherever any row does
+    row = np.arange(D, dtype=np.int64)
+    for rows_apart in (0, 1, V // 2, V - 2, V - 1, V):
+        for shift in (0, 1, D - 1, D, ld - D, ld - D + 1, ld - 1):
+            off = rows_apart * ld + shift      # in floats
+            r, c = np.divmod(row + off, ld)    # row and column in the other matrix
+            shared = bool(np.any((r < V) & (c < D)))
+            for a, b in ((base, base + 4 * off), (base + 4 * off, base)):
+                route = w2v.debug_step_route(*shape, in_ptr=a, out_ptr=b)
+                assert (route == "atomic") == shared, (rows_apart, shift)
+
+
+def test_step_route_refuses_invalid_arguments():
+    for bad in ((-1, 10, 5, 100, 64, 64), (1, -1, 5, 100, 64, 64), (1, 33, 5, 100, 64, 64),
+                (1, 10, 65, 100, 64, 64), (1, 10, 5, 0, 64, 64), (1, 10, 5, 100, 0, 64),
+                (1, 10, 5, 100, 64, 63)):
+        with pytest.raises(w2v.W2VError) as err:
+            w2v.debug_step_route(*bad)
+        assert err.value.code == w2v.EINVAL
+    with pytest.raises(w2v.W2VError):
+        w2v.debug_step_route(1, 10, 5, 100, 64, 64, in_ptr=0)
