@@ -433,6 +433,19 @@ __global__ __launch_bounds__(256) void k_part_fold(EpochArgs a) {
 // group (group_core.h) with up to OMAX output columns. Groups start at
 // retained indices that are multiples of G (G divides the 64-target
 // batches).
+
+// Sentences per SIMD of a default launch, as sentences_per_simd is for
+// k_epoch: part of what a launch computes, so it follows from C and OMAX (a
+// wavefront's rows: OMAX output rows, their updates and a block of input
+// rows) and not from what a build's registers leave. Builds use at most the
+// registers that allow it; k_epoch_grouped<4, 16> just fits two waves per
+// SIMD and runs one.
+constexpr int grouped_sentences_per_simd(int C, int omax) {
+  if (omax == 32) return 2;
+  if (omax == 16) return C == 1 ? 3 : C <= 3 ? 2 : 1;
+  return C <= 2 ? 3 : C <= 5 ? 2 : 1;
+}
+
 template <int C, int OMAX>
 __global__ __launch_bounds__(kWave) void k_epoch_grouped(EpochArgs a) {
   __shared__ SentenceLds sl;
@@ -746,11 +759,12 @@ bool grouped_shape_supported(int C, int omax) {
 int grouped_blocks_per_cu(int C, int omax, int K) {
   EpochKernel k = grouped_kernel_for(C, omax);
   if (k == nullptr) return 0;
-  // No more sentences at once than 160 KB of LDS hold at 11320 bytes and the
-  // negatives each: the concurrency is part of what a launch computes.
+  // The other part of the rule: no more sentences at once than 160 KB of LDS
+  // hold at 11320 bytes and the negatives each.
   const size_t per = (11320 + negatives_lds(K) + kLdsGranule - 1) / kLdsGranule * kLdsGranule;
+  const int by_rule = std::min(4 * grouped_sentences_per_simd(C, omax), (int)(kLdsPerCu / per));
   return std::min(resident_blocks_per_cu(reinterpret_cast<const void*>(k), negatives_lds(K)),
-                  (int)(kLdsPerCu / per));
+                  by_rule);
 }
 
 hipError_t launch_grouped(int C, int omax, const EpochArgs& a, int grid,

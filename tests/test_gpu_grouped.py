@@ -132,3 +132,20 @@ def test_hogwild_grouped_near_sequential(G):
     lo = eval_loss(o_in, o_out, t, ctx, negs)
     lg = eval_loss(gi.cpu().numpy(), go.cpu().numpy(), t, ctx, negs)
     assert abs(lg - lo) <= 0.02 * lo, (lg, lo)
+
+
+@pytest.mark.parametrize("G,K", [(2, 3), (4, 5), (2, 8), (8, 3), (4, 12), (8, 5), (2, 9),
+                                 (2, 14), (4, 20), (8, 24)])
+def test_default_concurrency_follows_the_stated_rule(G, K):
+    """Sentences in flight of a default launch over a vocabulary too large to
+    cap them: what the row registers of (C, capacity for G + K columns) and
+    160 KB of LDS leave, whatever registers a build happens to use."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    cap = 10 if G + K <= 10 else 16 if G + K <= 16 else 32
+    per_simd = {10: [3, 3, 2, 2, 2, 1, 1, 1], 16: [3, 2, 2, 1, 1, 1], 32: [2, 2]}[cap]
+    lds = -(-(11_320 + 256 * K) // 1280) * 1280
+    for C, waves in zip([1, 2, 3, 4, 5, 6, 8, 10], per_simd):
+        want = min(cus * min(4 * waves, 160 * 1024 // lds), 131_072 // (K + 1))
+        for D in (64 * C, 64 * C - 20):
+            assert w2v.default_inflight(D, 3, K, V=2**31 - 1, group=G) == want, D
