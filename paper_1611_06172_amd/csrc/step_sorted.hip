@@ -97,8 +97,30 @@ struct StageIo {
   }
 };
 
+// Waves per SIMD the registers of k_stage must allow (1: no bound). It is
+// bound by the rows in flight, and without a bound the compiler puts the
+// accumulators of the matrix instructions into registers of their own (AGPRs)
+// beside those of the rows, which costs the shapes below a wave or more
+// (k_stage<5, 10, true, false>: 217 + 88 registers and one wave, with the
+// bound 219 and two). Sorted batches of V = 100,000, Zipf(1.0) ids, us
+// without / with the bound: (65536, N 10, K 15, D 300) 1797 / 1547, (65536,
+// 10, 25, 200) 1990 / 1612, (65536, 32, 15, 128) 1932 / 1433, (65536, 10, 5,
+// 384) 1124 / 1104. Where no wave is lost the bound costs 1 to 2% ((65536,
+// 10, 5, 300) 982 / 996), and pulled batches have no such accumulators.
+// k_step, which the memory side's atomics bound, gained nothing from it.
+constexpr int stage_waves_per_eu(int C, int nmax, bool multi, bool pull) {
+  if (pull) return 1;
+  if (nmax == 10 && multi) return C == 1 ? 4 : C == 2 ? 3 : C <= 5 ? 2 : 1;
+  if (nmax == 10) return C == 2 ? 5 : C == 4 ? 4 : C == 6 ? 3 : 1;
+  if (nmax == 16 && multi) return C == 1 ? 4 : C == 2 ? 3 : C <= 4 ? 2 : 1;
+  if (nmax == 16) return C == 3 ? 4 : C == 4 ? 3 : 1;
+  return multi ? (C == 1 ? 3 : 2) : (C == 1 ? 5 : 1);
+}
+
 template <int C, int NMAX, bool kMulti, bool kPull>
-__global__ __launch_bounds__(kWave) void k_stage(SortedStepArgs a) {
+__global__ __launch_bounds__(kWave) __attribute__((
+    amdgpu_waves_per_eu(stage_waves_per_eu(C, NMAX, kMulti, kPull)))) void k_stage(
+    SortedStepArgs a) {
   const int lane = threadIdx.x;
   const int n_slots_out = a.K + 1;
   int64_t applied = 0, sum_n = 0, rejected = 0, rows = 0;
