@@ -1,6 +1,7 @@
 // C ABI of libw2v (declared in include/w2v.h): argument validation, error
 // reporting and kernel launches. Every check runs on the host before any HIP
 // call, so a rejected call has no device side effect.
+#include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -664,37 +665,68 @@ enum class StepRoute : int32_t {
   kPulled = W2V_STEP_ROUTE_PULLED,  // the same without staging rows: errors kept, updates formed again
 };
 
-// The fastest route that the workspace (two fp64 V x ld buffers) allows, by
-// estimates fitted to one MI355X (us measured / estimated at B, N, K, V, D):
-//   atomic  clearing and applying 4 V ld fp64 values at 4.8 TB/s, and per
-//           updated row 0.74 ns and 39 ps for each 64-byte atomic request
-//           (eight fp64 values), under Zipf(1.0) ids (65536, 10, 5, 1e5, 300:
-//           2580 / 2550; 65536, 10, 5, 1e5, 100: 1390 / 1400; 4096, 10, 5,
-//           1e4, 300: 184 / 182; 64, 10, 5, 1e5, 300: 235 / 231);
-//   staged  2.8 ps per staged element and 90 us of launches and of the chain
-//           of 64 entries per wavefront (16384, 10, 5, 1e5, 300: 295 / 310;
-//           4096: 124 / 145; 512: 104 / 97);
-//   pulled  2 N (K + 1) partner rows a minibatch at 35 + 0.2 D ps each, at
-//           least 250 us for the chain of a wavefront, and 120 us beside it
-//           (65536, 10, 5, 1e5, 300: 992 / 870; 65536, 10, 25, 1e5, 300:
-//           3180 / 3360; 4096, 10, 5, 1e4, 300: 360 / 370).
+// Time of a route, us, by estimates fitted to 23,900 random shapes on one
+// MI355X (B 32 to 150,000, N 1 to 32, K 0 to 63, V 2,000 to 10^6, D 8 to 640;
+// a tenth off in the mean), under Zipf(1.0) ids and under uniform ones. The
+// ids are on the device, so the host does not know which they are; what their
+// concentration changes is how atomics to one row queue (0.57 against 0.07 ns
+// per updated row beside 46 ps for each 64-byte request) and whether a pulled
+// batch finds its partner rows in L2 (0.22 against 0.54 ps per element).
+struct RouteTimes {
+  double atomic, staged, pulled;
+};
+
+static RouteTimes route_times(int32_t B, int32_t N, int32_t K, int32_t V, int32_t D,
+                              int32_t ld, bool zipf) {
+  const double n = (double)B * ((double)N + K + 1);  // updated rows
+  const double C = (D + 63) / 64;
+  RouteTimes t;
+  // clearing and applying the delta buffers (5 TB/s), and the atomics
+  t.atomic = 28.0 + 6.3e-6 * (double)V * ld +
+             n * ((zipf ? 0.57e-3 : 0.07e-3) + (zipf ? 47e-6 : 45e-6) * ((D + 7) / 8));
+  // about 20 launches; a minibatch's and a reduction's chain; the staging
+  // rows and the sort
+  const double latency = 3.5 * C + 0.48 * (K + 1);
+  const double staging = n * (0.21e-3 + (zipf ? 2.2e-6 : 3.0e-6) * D);
+  t.staged = 90.0 + sqrt(latency * latency + staging * staging);
+  // a wavefront's chain of 64 entries, four partner rows at a time, twice;
+  // 2 N (K + 1) partner rows a minibatch and the sort
+  const double chain = 64.0 * ((K + 4) / 4 + (N + 3) / 4) * (zipf ? 0.26 : 0.34) *
+                       (1.0 + 0.14 * C);
+  const double rows = 2.0 * (double)B * N * (K + 1) *
+                          (8.4e-6 + (zipf ? 0.22e-6 : 0.54e-6) * D) +
+                      0.385e-3 * n;
+  t.pulled = 146.0 + cbrt(chain * chain * chain + rows * rows * rows);
+  return t;
+}
+
+// The route that the workspace (two fp64 V x ld buffers) allows and whose
+// larger loss, under Zipf ids or under uniform ones, is the smallest, but none
+// that is slower than the atomic route under Zipf ids. Measured on the shapes
+// of the fit, against the atomic route alone: 1.50 times as fast in the mean
+// under Zipf ids and 1.39 times under uniform ones; more than a fifth slower
+// for 0.5% and 2.5% of the shapes (a rule for Zipf ids alone left 7.6% of the
+// shapes that much slower under uniform ones, up to 6.9 times).
 static StepRoute step_route(int32_t B, int32_t N, int32_t K, const float* M_in,
                             const float* M_out, int32_t V, int32_t D, int32_t ld) {
   const size_t workspace = w2v_step_batch_workspace_bytes(V, ld);
   const int64_t n = (int64_t)B * ((int64_t)N + K + 1);
   if (n > INT32_MAX || rows_overlap(M_in, M_out, V, D, ld)) return StepRoute::kAtomic;
-  const double atomic_us = 15.0 + 32.0 * (double)V * ld / 4.8e6 +
-                           (double)n * (0.74e-3 + 39e-6 * ((D + 7) / 8));
-  const double staged_us = 90.0 + (double)n * D * 2.8e-6;
-  const double rows_us = 2.0 * (double)B * N * (K + 1) * (35e-6 + 0.2e-6 * D);
-  const double pulled_us = 120.0 + (rows_us > 250.0 ? rows_us : 250.0);
+  const RouteTimes z = route_times(B, N, K, V, D, ld, true);
+  const RouteTimes u = route_times(B, N, K, V, D, ld, false);
+  StepRoute route = StepRoute::kAtomic;
+  double least = z.atomic * u.atomic;  // of two routes, the smaller product
+                                       // has the smaller worst loss
+  if (z.staged <= z.atomic && z.staged * u.staged < least &&
+      sorted_step_workspace_bytes(B, N, K, V, ld, false) <= workspace) {
+    route = StepRoute::kStaged;
+    least = z.staged * u.staged;
+  }
   // a partner per lane: at most 64 output columns
-  const bool pull_ok = K < 64 && pulled_us < atomic_us &&
-                       sorted_step_workspace_bytes(B, N, K, V, ld, true) <= workspace;
-  if (staged_us < atomic_us && (!pull_ok || staged_us < pulled_us) &&
-      sorted_step_workspace_bytes(B, N, K, V, ld, false) <= workspace)
-    return StepRoute::kStaged;
-  return pull_ok ? StepRoute::kPulled : StepRoute::kAtomic;
+  if (K < 64 && z.pulled <= z.atomic && z.pulled * u.pulled < least &&
+      sorted_step_workspace_bytes(B, N, K, V, ld, true) <= workspace)
+    route = StepRoute::kPulled;
+  return route;
 }
 
 }  // namespace w2v

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,N,K,V,D,route", [
-    (25_000, 10, 5, 60_000, 64, "pulled"),
+    (12_000, 10, 5, 15_000, 300, "pulled"),
     (1_500, 10, 5, 100_000, 300, "staged"),
     (300, 10, 5, 3_000, 64, "atomic"),
 ])

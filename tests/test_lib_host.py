@@ -259,3 +259,23 @@ def test_step_route_refuses_invalid_arguments():
         assert err.value.code == w2v.EINVAL
     with pytest.raises(w2v.W2VError):
         w2v.debug_step_route(1, 10, 5, 100, 64, 64, in_ptr=0)
+
+
+@pytest.mark.parametrize("shape,route", [
+    # the atomic route is the fastest under uniform ids, by far, and about as
+    # fast as the others (or faster) under Zipf ids
+    ((16_384, 32, 15, 100_000, 128, 128), "atomic"),   # us 961 / 737 (Zipf / uniform), pulled 889 / 1453
+    ((16_384, 16, 25, 100_000, 200, 224), "atomic"),   # 1215 / 1020, pulled 1026 / 1989
+    ((8_989, 2, 63, 52_569, 37, 64), "atomic"),        # 148 / 96, pulled 537 / 663
+    ((18_079, 29, 0, 97_691, 13, 32), "atomic"),       # 282 / 124, pulled 470 / 511
+    ((64, 10, 5, 20_000, 600, 608), "atomic"),         # 100 / 100, staged 129 / 123
+    ((256, 10, 5, 20_000, 640, 640), "atomic"),        # 111, staged 135
+    # the others are the fastest under both
+    ((65_536, 10, 5, 100_000, 300, 320), "pulled"),    # 2598 / 2096, pulled 1021 / 1798
+    ((16_384, 10, 5, 1_000_000, 300, 320), "staged"),  # 2560 / 2673, staged 323 / 441
+    ((1_024, 10, 5, 100_000, 300, 320), "staged"),     # 283 / 279, staged 118 / 117
+    # a loss under uniform ids that the gain under Zipf ids outweighs
+    ((16_384, 10, 15, 100_000, 300, 320), "pulled"),   # 1137 / 1042, pulled 616 / 1209
+])
+def test_step_route_weighs_both_distributions(shape, route):
+    assert w2v.debug_step_route(*shape) == route
