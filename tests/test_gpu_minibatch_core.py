@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 from paper_1611_06172_amd import inputs, w2v
-from gpu_util import expect_device_flag, scaled_error, to_dev
+from gpu_util import scaled_error, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -73,48 +73,3 @@ def test_serialised_epoch_at_block_borders(window, K, D):
         d = np.abs(g.cpu().numpy().astype(np.float64) - o)
         scale = np.abs(o).max(axis=1, keepdims=True) + 1e-3 * np.abs(o).max()
         assert float((d / scale).max()) < 2e-4
-
-
-@pytest.mark.parametrize("B,N,K,V,D,pad,absent", [
-    (25_000, 10, 5, 60_000, 64, 0, 0.0),      # updates formed again (pulled)
-    (20_000, 10, 5, 50_000, 100, 3, 0.3),     # the same, unaligned rows, gaps
-    (40_000, 3, 7, 50_000, 63, 0, 0.0),       # several blocks, several chunks
-    (30_000, 12, 1, 90_000, 20, 12, 0.1),
-    (1_500, 10, 5, 100_000, 64, 0, 0.2),      # staging rows fit the workspace
-    (70, 2, 0, 3_000, 385, 15, 0.0),
-    (2_000, 10, 5, 300, 64, 0, 0.0),          # delta buffers and atomics
-])
-def test_every_route_of_the_snapshot_batch(B, N, K, V, D, pad, absent):
-    """w2v_step_batch by whatever route its sizes take: the oracle's result,
-    the sorted batch's to the last bit of a sum rounded once, skipped
-    minibatches counted, untouched elements and row padding bit for bit."""
-    import torch
-    t, c, n = inputs.kernel_batch(B, N, K, V, 1.0, 7)
-    rng = np.random.Generator(np.random.PCG64(8))
-    c[rng.random(c.shape) < absent] = -1
-    t[1], c[3, 0] = V, -2                      # two minibatches are skipped
-    bad = [1, 3]
-    M_in = inputs.init_matrix(V, D, "normal", 4)
-    M_out = inputs.init_matrix(V, D, "normal", 5)
-    ok = np.setdiff1d(np.arange(B), bad)
-    oi, oo, S_in, S_out = oracle.step_batch(t[ok], c[ok], n[ok], M_in, M_out, 0.025)
-    got = []
-    for srt in (False, True):
-        full = [torch.full((V, D + pad), 9.0, device="cuda") for _ in range(2)]
-        m = [f[:, :D] for f in full]
-        for x, y in zip(m, (M_in, M_out)):
-            x.copy_(to_dev(y))
-        stats = torch.zeros(5, dtype=torch.int64, device="cuda")
-        w2v.step_batch(to_dev(t), to_dev(c), to_dev(n), m[0], m[1], 0.025, stats=stats,
-                       sorted=srt)
-        expect_device_flag()
-        got.append([x.cpu().numpy() for x in m] + [stats.cpu().numpy()])
-        assert all(bool((f[:, D:] == 9.0).all()) for f in full)
-    for g, o, S, M0 in zip(got[0], (oi, oo), (S_in, S_out), (M_in, M_out)):
-        assert scaled_error(g, o, S) <= BAR
-        rest = o == M0
-        assert np.array_equal(g[rest], M0[rest])
-    assert np.array_equal(got[0][2], got[1][2]) and got[0][2][3] == len(bad)
-    # fp64 sums in another order, rounded once: one fp32 step apart at most
-    for g, h in zip(got[0][:2], got[1][:2]):
-        assert np.all(np.abs(g - h) <= np.spacing(np.maximum(np.abs(g), np.abs(h))))
