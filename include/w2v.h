@@ -216,7 +216,8 @@ int32_t w2v_pending_slots(int32_t D, int32_t window, int32_t K);
  * + pending updates) while its word is in the window, and adds the slot to
  * M_in atomically when it releases the word: when the slot is needed for
  * another word, when 2 * window targets have passed without the word and the
- * next one does not hold it either, and at the end of the sentence. Every update reaches M_in before the call returns.
+ * next one does not hold it either, and at the end of the sentence. Every
+ * update reaches M_in before the call returns.
  * With one sentence in flight this changes only the order of the fp32
  * additions; with several, another sentence sees these updates late (as
  * late as the word stays in this sentence's window) and never loses them.
@@ -385,7 +386,8 @@ int w2v_debug_minibatches(const int32_t* corpus, int64_t T, int64_t pos_begin,
                           uint8_t* out_mask, float* out_alpha, int64_t* stats,
                           void* stream);
 
-/* Bytes of workspace w2v_step_batch needs: two fp64 V x ld delta buffers. */
+/* Bytes of workspace w2v_step_batch needs: the size of two fp64 V x ld
+ * buffers, each rounded up to 256 bytes. */
 size_t w2v_step_batch_workspace_bytes(int32_t V, int32_t ld);
 
 /*
@@ -400,15 +402,22 @@ size_t w2v_step_batch_workspace_bytes(int32_t V, int32_t ld);
  * the whole batch shares that snapshot, so the result does not depend on the
  * order of the minibatches (a deterministic counterpart of the Hogwild
  * epoch, not a step the paper runs as such). The per-minibatch updates are
- * summed per element in fp64 (in `workspace`) and each touched element
- * becomes fp32(M + sum), one rounding per element. Elements whose summed
- * update is exactly 0 keep their bits.
+ * summed per element in fp64 and each touched element becomes fp32(M + sum),
+ * one rounding per element. Elements whose summed update is exactly 0 keep
+ * their bits. How the sums are formed follows from the sizes: with fp64
+ * atomics into delta buffers (in arrival order, so the last fp32 bit of an
+ * element may differ from run to run), from staging rows, or from the
+ * minibatches' errors; only w2v_step_batch_sorted promises the same bits on
+ * every run. M_in and M_out may share elements (one matrix passed as both,
+ * overlapping views): a shared element receives both updates, rounded one
+ * after the other.
  * targets: device int32[B]; contexts: device int32[B][N], -1 = absent;
  * negatives: device int32[B][K]; a negative equal to its target is masked.
  * alpha: device float[B], or NULL to use alpha_scalar for every minibatch.
  * workspace: device, >= w2v_step_batch_workspace_bytes(V, ld) bytes, 256-byte
- * aligned. stats: device int64[5] or NULL, as in w2v_train_epoch ([2] is
- * not used).
+ * aligned, caller-owned scratch of no stated layout: its contents need not be
+ * initialised, and calls that overlap in time must not share it. stats:
+ * device int64[5] or NULL, as in w2v_train_epoch ([2] is not used).
  * Limits: 0 <= N <= W2V_MAX_BATCH_INPUTS, 0 <= K <= W2V_MAX_NEGATIVE,
  * 1 <= D <= W2V_MAX_DIM.
  */
@@ -442,10 +451,12 @@ size_t w2v_step_batch_sorted_workspace_bytes(int32_t B, int32_t N, int32_t K,
  * are written to staging rows, sorted by row id with a stable radix sort
  * (so a row's updates stay in minibatch order) and summed per row in fp64
  * in that order, in chunks of 64 whose partial sums are added in chunk
- * order (grouped 32 chunks at a time). The result is the same bits on every run, and no atomics are
- * used. It may differ from w2v_step_batch, whose fp64 atomics add in
- * arrival order, in the last fp32 bit of an element.
- * Additional limit: B (N + K + 1) must fit in int32. workspace: device,
+ * order (grouped 32 chunks at a time). The result is the same bits on every
+ * run, and no atomics are used. w2v_step_batch gives the same bits where it
+ * takes no atomics either, and may differ in the last fp32 bit of an element
+ * where it does.
+ * Additional limits: B (N + K + 1) must fit in int32, and M_in and M_out must
+ * not share elements. workspace: device,
  * >= w2v_step_batch_sorted_workspace_bytes(B, N, K, V, ld) bytes, 256-byte
  * aligned, caller-owned, contents need not be initialised; calls that
  * overlap in time must not share it.

@@ -660,9 +660,12 @@ static bool rows_overlap(const float* M_in, const float* M_out, int32_t V, int32
 // How w2v_step_batch sums the updates of a row, all three in fp64 with one
 // rounding per element.
 enum class StepRoute : int32_t {
-  kAtomic = W2V_STEP_ROUTE_ATOMIC,  // fp64 atomics into V x ld delta buffers, cleared and applied whole
-  kStaged = W2V_STEP_ROUTE_STAGED,  // the sorted batch: staging rows, summed per row
-  kPulled = W2V_STEP_ROUTE_PULLED,  // the same without staging rows: errors kept, updates formed again
+  // fp64 atomics into V x ld delta buffers, cleared and applied whole
+  kAtomic = W2V_STEP_ROUTE_ATOMIC,
+  // the sorted batch: staging rows, summed per row
+  kStaged = W2V_STEP_ROUTE_STAGED,
+  // the same without staging rows: errors kept, updates formed again
+  kPulled = W2V_STEP_ROUTE_PULLED,
 };
 
 // Time of a route, us, by estimates fitted to 23,900 random shapes on one

@@ -138,11 +138,12 @@ __device__ __forceinline__ float f_pair_dpp(float a, float b, bool upper) {
   return keep + f_dpp<kCtrl>(send);
 }
 
-// Transposing reduction of 64 values per lane. On return, lane l holds
-// sum over all 64 lanes of v[l]. The partner of each step differs from the
-// lane in exactly the bit being split (32, 16, then 8, 4, 2, 1 via mirrors),
-// so the six steps together cover every lane once. The steps after the
-// first (32 values left):
+// Transposing reduction of 64 values per lane (xpose_reduce64_lazy). On
+// return, lane l holds the sum over all 64 lanes of value l. The partner of
+// each step differs from the lane in the bit being split (32, 16, then 8, 4,
+// 2, 1 via mirrors, which also flip lower bits that later steps sum over), so
+// the six steps together cover every lane once. The steps after the first (32
+// values left):
 __device__ __forceinline__ float xpose_tail32(float (&v)[32], int lane) {
 #pragma unroll
   for (int j = 0; j < 16; ++j) v[j] = f_swap_sum16(v[j], v[j + 16]);
@@ -159,10 +160,9 @@ __device__ __forceinline__ float xpose_tail32(float (&v)[32], int lane) {
   return f_pair_dpp<kDppXor1>(v[0], v[1], b0);
 }
 
-// Value s is produced on demand by value(s) (s a
-// compile-time index after unrolling), so that values s and s + 32 are
-// formed just before the first step combines them and at most 32 partial
-// sums are live at once.
+// Value s is produced on demand by value(s) (s a compile-time index after
+// unrolling), so that values s and s + 32 are formed just before the first
+// step combines them and at most 32 partial sums are live at once.
 template <class F>
 __device__ __forceinline__ float xpose_reduce64_lazy(F&& value, int lane) {
   float w[32];
@@ -197,10 +197,6 @@ __device__ __forceinline__ float lane_value(float x, int l) {
 
 __device__ __forceinline__ int uniform_int(int x) {
   return __builtin_amdgcn_readfirstlane(x);
-}
-
-__device__ __forceinline__ float uniform_float(float x) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 
 __device__ __forceinline__ uint64_t lanes_below(int lane) {

@@ -260,15 +260,22 @@ struct EpochIo {
 // that the row registers of a shape leave, times the four SIMDs. How far
 // concurrent sentences drift from the sequential epoch depends on how many
 // there are, so this is part of what a launch computes, not only of how fast
-// it does: it follows from C and the size of a logit block alone, and the
-// registers below are held to it.
+// it does: it follows from C, the capacity of input rows and whether the N x
+// (K + 1) logits fit one reduction of 64 (several_blocks), and it stays as it
+// is when the kernels change. The kernels' own output blocks are another
+// matter: Core takes up to 6 columns in one block whatever nmax is, so a
+// one-block kernel of nmax 16 or 32 serves K on both sides of this rule, and
+// its registers allow the larger of the two values.
+constexpr bool several_blocks_of(int nmax, int K) { return K + 1 > kWave / nmax; }
+
 constexpr int sentences_per_simd(int C, int nmax, bool several_blocks) {
   if (nmax == 32) return !several_blocks && C == 1 ? 3 : 2;
   if (nmax == 16) return several_blocks ? (C == 1 ? 3 : C <= 3 ? 2 : 1) : C <= 2 ? 3 : 2;
   return several_blocks ? (C <= 2 ? 3 : C <= 5 ? 2 : 1) : C <= 4 ? 3 : 2;
 }
 
-// Waves per SIMD the register allocation must allow.
+// Waves per SIMD the register allocation must allow: the most sentences per
+// SIMD that a launch of the kernel runs.
 template <int C, int NMAX, bool kMulti>
 constexpr int epoch_waves_per_eu() {
   return sentences_per_simd(C, NMAX, kMulti);
@@ -686,14 +693,13 @@ static TrainShape compute_train_shape(int C, int nmax, int K) {
   EpochKernel k = train_kernel_for(C, nmax, K);
   if (k == nullptr) return t;
   const void* f = reinterpret_cast<const void*>(k);
-  const int best = std::min(resident_blocks_per_cu(f, negatives_lds(K, 8)),
-                       4 * sentences_per_simd(C, nmax, K + 1 > kWave / nmax));
+  const int by_rule = 4 * sentences_per_simd(C, nmax, several_blocks_of(nmax, K));
+  const int best = std::min(resident_blocks_per_cu(f, negatives_lds(K, 8)), by_rule);
   while (t.target_batch > 8 &&
          resident_blocks_per_cu(f, negatives_lds(K, t.target_batch)) < best)
     t.target_batch /= 2;
   const size_t negs = negatives_lds(K, t.target_batch);
-  t.blocks_per_cu = std::min(resident_blocks_per_cu(f, negs),
-                        4 * sentences_per_simd(C, nmax, K + 1 > kWave / nmax));
+  t.blocks_per_cu = std::min(resident_blocks_per_cu(f, negs), by_rule);
   if (t.blocks_per_cu <= 0) return t;
   for (int n = kMaxPendingSlots; n >= 2; --n)
     if (resident_blocks_per_cu(f, negs + n * slot_bytes(C)) >= t.blocks_per_cu) {

@@ -50,19 +50,15 @@
 // the matrix row plus every partial row, so atomics to one address come from
 // one XCD only and nothing is hidden from a reader. Snapshot batches add
 // their updates with fp64 atomics into a delta buffer instead, or write them
-// to staging rows for a sorted reduction (StagedRows).
+// to staging rows for a sorted reduction.
 //
-// Pending input-row updates (PendingRows): consecutive targets of a
-// sentence share most of their input words, so a training wavefront adds
-// the updates of a cold input row to an LDS slot instead of the matrix, reads
-// the row as (matrix row + its pending updates) while the word stays in the
-// window, and adds the slot to the matrix once, atomically, when it lets
-// the word go. The row traffic of the minibatch path is dominated by its
-// writes; this turns about 2 window writes of an input row into one.
+// Where rows are read and where updates go is the business of the caller's Io
+// (EpochIo, with the pending input-row updates, in the epoch kernel; StepIo
+// and StageIo in the snapshot batches).
 //
 // Output columns go in blocks of KB: 6 where the K + 1 columns fit (the
-// paper's K = 5), all of them in one block, else 8 with the update of the
-// input rows accumulated over the blocks.
+// paper's K = 5), all of them in one block, else 8 (4 for rows of more than
+// 384 columns) with the update of the input rows accumulated over the blocks.
 #pragma once
 
 #include "device_common.h"
@@ -438,7 +434,7 @@ __device__ __forceinline__ float target_error(bool is_target, float x, float wgt
 }
 
 // The fused minibatch. C: columns per lane; NMAX: input rows (10, 16 or 32);
-// kMulti: several output blocks of 8 columns, else one of 6 (K <= 5). Io
+// kMulti: several output blocks of KB columns, else one of 6 (K <= 5). Io
 // says where rows are read and where updates go:
 //   load_in(id, ok, row), load_out(id, ok, row): issue the loads of a row
 //     (zeros where !ok, without touching memory);

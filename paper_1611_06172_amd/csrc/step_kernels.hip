@@ -1,6 +1,6 @@
 // Snapshot batch of independent HogBatch minibatches on gfx950: the route
-// with atomics (w2v_step_batch takes it where its sizes make it the fastest;
-// the others are in step_sorted.hip).
+// with atomics (w2v_step_batch takes it where its sizes make it the fastest
+// and where the matrices share elements; the others are in step_sorted.hip).
 //
 // Three launches on the caller's stream:
 //   1. zero the fp64 delta buffers (workspace);

@@ -426,7 +426,8 @@ def step_batch(targets, contexts, negatives, M_in, M_out, alpha=0.025, *,
                stream=None, sorted: bool = False):
     """One snapshot batch of B minibatches; updates M_in, M_out in place.
     sorted: sum each row's updates in a fixed order (w2v_step_batch_sorted:
-    the same bits on every run) instead of with fp64 atomics."""
+    the same bits on every run) instead of by the way that is the fastest for
+    the sizes, which may be fp64 atomics in arrival order."""
     import torch
     _dev(targets, torch.int32, "targets", 1)
     _dev(contexts, torch.int32, "contexts", 2)
