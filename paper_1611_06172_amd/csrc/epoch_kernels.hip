@@ -322,8 +322,8 @@ __global__ __launch_bounds__(kWave) __attribute__((
 
     for (int q0 = 0; q0 < n_ret; q0 += TB) {
       uint64_t bad;
-      const FormedTarget t = form_targets(reread_args(), sb, q0, n_ret, lane, sl, negs_lds,
-                                          TB, bad);
+      const FormedTarget t = form_targets<false>(reread_args(), sb, q0, n_ret, lane, sl,
+                                                 negs_lds, TB, bad);
       uint64_t todo = __ballot(t.n > 0);
       rejected += __popcll(todo & bad);
       todo &= ~bad;
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(kWave) void k_export(EpochArgs a) {
     for (int q0 = 0; q0 < n_ret; q0 += kWave) {
       uint64_t bad;
       const FormedTarget t =
-          form_targets(a, sb, q0, n_ret, lane, sl, negs_lds, kWave, bad);
+          form_targets<false>(a, sb, q0, n_ret, lane, sl, negs_lds, kWave, bad);
       export_targets(a, sb, q0, n_ret, lane, sl, t, negs_lds);
       const uint64_t formed = __ballot(t.n > 0);
       rejected += __popcll(formed & bad);
@@ -477,7 +477,7 @@ __global__ __launch_bounds__(kWave) void k_epoch_grouped(EpochArgs a) {
     const int n_ret = keep_and_compact<false>(a, sb, len, lane, sl, rejected);
 
     for (int q0 = 0; q0 < n_ret; q0 += kWave) {
-      form_target_batch(a, sb, q0, n_ret, lane, sl, tb, negs_lds);
+      form_target_batch<(C >= 6)>(a, sb, q0, n_ret, lane, sl, tb, negs_lds);
       const int cnt = min(kWave, n_ret - q0);
       for (int j0 = 0; j0 < cnt; j0 += G) {
         // Members: lane g < G holds the input count of target j0 + g.

@@ -77,8 +77,8 @@ __global__ __launch_bounds__(kWave) void k_epoch_pairwise(EpochArgs a) {
       EpochArgs targets_only = a;
       targets_only.K = 0;
       uint64_t unused;
-      const FormedTarget t = form_targets(targets_only, sb, q0, n_ret, lane, sl, negs_lds,
-                                          kWave, unused);
+      const FormedTarget t = form_targets<false>(targets_only, sb, q0, n_ret, lane, sl,
+                                                 negs_lds, kWave, unused);
       for (uint64_t todo = __ballot(t.n > 0); todo != 0ull; todo &= todo - 1ull) {
         const int j = __builtin_ctzll(todo);
         const int n = __builtin_amdgcn_readlane(t.n, j);

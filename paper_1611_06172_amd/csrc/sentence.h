@@ -88,12 +88,16 @@ struct FormedTarget {
 // lane j returns target j, its negatives go to negs[j K + k], and `bad` gets
 // bit j where one of them is outside [0, V). The 64 / TB lanes l = j mod TB
 // share target j: lane l takes every (64 / TB)-th Philox block from block
-// l / TB on, and the table reads of a block are all in flight before any is
-// used (one by one, each a random access to a table of up to 400 MB, they
-// were 7% of the epoch's cycles at K = 64). For that they are issued without
-// a branch, a word that is no negative reading entry 0: behind a test for
-// each the compiler waits for one read before the next (grouped epoch, D =
-// 384, G = 4, 4e6 tokens: 24.7 ms with the tests, 22.4 without).
+// l / TB on. The table reads of a block (each a random access to a table of
+// up to 400 MB) come before any use of one. With kTogether they are issued
+// without a branch, a word that is no negative reading entry 0, and are all
+// in flight at once; else each stands behind its test, so nothing is read in
+// vain, but the compiler waits for some of them before it issues the next.
+// That wait shows where a SIMD holds one wavefront with little else to do
+// (grouped epoch, D = 384, G = 4, K = 5, 4e6 tokens: 24.6 ms behind the tests,
+// 22.6 together); elsewhere reading together changes the times by 2% either
+// way (planted shape, K = 25: 81.4 / 80.2 ms; D = 485, K = 25: 107.7 / 109.5).
+template <bool kTogether>
 __device__ __forceinline__ FormedTarget form_targets(const EpochArgs& a, int64_t sb,
                                                      int q0, int n_ret, int lane,
                                                      const SentenceLds& sl,
@@ -123,16 +127,21 @@ __device__ __forceinline__ FormedTarget form_targets(const EpochArgs& a, int64_t
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int k = k0 + i;
-        const uint64_t at = scale_draw(word_of(blk, i), (uint64_t)a.table_size);
-        neg[i] = a.table[k >= 0 && k < K ? at : 0];
+        if constexpr (kTogether) {
+          const uint64_t at = scale_draw(word_of(blk, i), (uint64_t)a.table_size);
+          neg[i] = a.table[k >= 0 && k < K ? at : 0];
+          if (k < 0 || k >= K) neg[i] = 0;
+        } else {
+          neg[i] = 0;
+          if (k >= 0 && k < K)
+            neg[i] = a.table[scale_draw(word_of(blk, i), (uint64_t)a.table_size)];
+        }
       }
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int k = k0 + i;
-        if (k >= 0 && k < K) {
-          bad_id |= neg[i] < 0 || neg[i] >= a.V;
-          negs[j * K + k] = neg[i];
-        }
+        bad_id |= neg[i] < 0 || neg[i] >= a.V;
+        if (k >= 0 && k < K) negs[j * K + k] = neg[i];
       }
     }
     t.alpha = decayed_alpha(a.alpha0, a.min_frac, a.epoch, a.n_epochs, a.T, p);
@@ -149,12 +158,14 @@ __device__ __forceinline__ FormedTarget form_targets(const EpochArgs& a, int64_t
 }
 
 // The same for the 64 targets q0 .. q0 + 63, into LDS.
+template <bool kTogether>
 __device__ __forceinline__ void form_target_batch(const EpochArgs& a, int64_t sb,
                                                   int q0, int n_ret, int lane,
                                                   const SentenceLds& sl,
                                                   TargetBatch& tb, int32_t* negs) {
   uint64_t bad;
-  const FormedTarget t = form_targets(a, sb, q0, n_ret, lane, sl, negs, kWave, bad);
+  const FormedTarget t =
+      form_targets<kTogether>(a, sb, q0, n_ret, lane, sl, negs, kWave, bad);
   tb.lo[lane] = t.lo;
   tb.n[lane] = t.n;
   tb.alpha[lane] = t.alpha;
