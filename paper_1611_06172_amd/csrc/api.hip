@@ -672,9 +672,8 @@ enum class StepRoute : int32_t {
 // MI355X (B 32 to 150,000, N 1 to 32, K 0 to 63, V 2,000 to 10^6, D 8 to 640;
 // a tenth off in the mean), under Zipf(1.0) ids and under uniform ones. The
 // ids are on the device, so the host does not know which they are; what their
-// concentration changes is how atomics to one row queue (0.57 against 0.07 ns
-// per updated row beside 46 ps for each 64-byte request) and whether a pulled
-// batch finds its partner rows in L2 (0.22 against 0.54 ps per element).
+// concentration changes is how atomics to the most frequent row queue and how
+// many rows come from L2 and the memory-side cache instead of memory.
 struct RouteTimes {
   double atomic, staged, pulled;
 };
@@ -683,22 +682,37 @@ static RouteTimes route_times(int32_t B, int32_t N, int32_t K, int32_t V, int32_
                               int32_t ld, bool zipf) {
   const double n = (double)B * ((double)N + K + 1);  // updated rows
   const double C = (D + 63) / 64;
+  const double requests = (D + 7) / 8;  // 64-byte atomic requests of a row
+  // doublings of one matrix's bytes over an XCD's L2
+  const double size = log2((double)V * ld * 4.0 / (4 << 20));
+  const double doublings = size < 0.0 ? 0.0 : size > 9.0 ? 9.0 : size;
   RouteTimes t;
-  // clearing and applying the delta buffers (5 TB/s), and the atomics
-  t.atomic = 28.0 + 6.3e-6 * (double)V * ld +
-             n * ((zipf ? 0.57e-3 : 0.07e-3) + (zipf ? 47e-6 : 45e-6) * ((D + 7) / 8));
+  // Clearing and applying the delta buffers (5 TB/s), then the atomics: under
+  // Zipf ids with the queue at the most frequent row, which the share 1 - (1 -
+  // p)^slots of the minibatches update.
+  t.atomic = 28.0 + 6.3e-6 * (double)V * ld;
+  if (zipf) {
+    const double p = 1.0 / (log((double)V) + 0.577);
+    const double slots = N > K + 1 ? N : K + 1;
+    t.atomic += n * (0.133e-3 + 39.3e-6 * requests) +
+                B * (1.0 - pow(1.0 - p, slots)) *
+                    (2.75e-3 + 3.41e-3 * (requests < 4.0 ? requests : 4.0));
+  } else {
+    t.atomic += n * (0.075e-3 + (40.8e-6 + 1.24e-6 * doublings) * requests);
+  }
   // about 20 launches; a minibatch's and a reduction's chain; the staging
   // rows and the sort
-  const double latency = 3.5 * C + 0.48 * (K + 1);
-  const double staging = n * (0.21e-3 + (zipf ? 2.2e-6 : 3.0e-6) * D);
-  t.staged = 90.0 + sqrt(latency * latency + staging * staging);
+  const double latency = 3.5 * C + 0.47 * (K + 1);
+  const double staging =
+      n * (0.235e-3 + (zipf ? 0.3e-6 + 0.29e-6 * doublings : 0.48e-6 * doublings) * D);
+  t.staged = 91.0 + sqrt(latency * latency + staging * staging);
   // a wavefront's chain of 64 entries, four partner rows at a time, twice;
   // 2 N (K + 1) partner rows a minibatch and the sort
-  const double chain = 64.0 * ((K + 4) / 4 + (N + 3) / 4) * (zipf ? 0.26 : 0.34) *
+  const double chain = 64.0 * ((K + 4) / 4 + (N + 3) / 4) * (zipf ? 0.26 : 0.335) *
                        (1.0 + 0.14 * C);
-  const double rows = 2.0 * (double)B * N * (K + 1) *
-                          (8.4e-6 + (zipf ? 0.22e-6 : 0.54e-6) * D) +
-                      0.385e-3 * n;
+  const double element = zipf ? 0.11e-6 + 0.0202e-6 * doublings : 0.134e-6 + 0.0794e-6 * doublings;
+  const double rows =
+      2.0 * (double)B * N * (K + 1) * (9.2e-6 + element * D) + 0.39e-3 * n;
   t.pulled = 146.0 + cbrt(chain * chain * chain + rows * rows * rows);
   return t;
 }
@@ -706,9 +720,9 @@ static RouteTimes route_times(int32_t B, int32_t N, int32_t K, int32_t V, int32_
 // The route that the workspace (two fp64 V x ld buffers) allows and whose
 // larger loss, under Zipf ids or under uniform ones, is the smallest, but none
 // that is slower than the atomic route under Zipf ids. Measured on the shapes
-// of the fit, against the atomic route alone: 1.50 times as fast in the mean
+// of the fit, against the atomic route alone: 1.51 times as fast in the mean
 // under Zipf ids and 1.39 times under uniform ones; more than a fifth slower
-// for 0.5% and 2.5% of the shapes (a rule for Zipf ids alone left 7.6% of the
+// for 0.6% and 3.0% of the shapes (a rule for Zipf ids alone left 7.6% of the
 // shapes that much slower under uniform ones, up to 6.9 times).
 static StepRoute step_route(int32_t B, int32_t N, int32_t K, const float* M_in,
                             const float* M_out, int32_t V, int32_t D, int32_t ld) {

@@ -58,12 +58,12 @@ BAR = 1e-5
     (10_000, 10, 5, 8_000, 400, 0, 0.0, "pulled"),      # C = 8, one block
     (6_000, 10, 12, 30_000, 600, 40, 0.0, "pulled"),    # C = 10, blocks of 4
     (25_000, 1, 1, 3_000, 640, 0, 0.0, "pulled"),       # fewest partners
-    (16_000, 1, 63, 100_000, 64, 0, 0.0, "pulled"),     # a partner in every lane
+    (12_000, 1, 63, 50_000, 100, 0, 0.0, "pulled"),     # a partner in every lane
     (1_500, 10, 5, 100_000, 300, 20, 0.2, "staged"),
     (2_500, 20, 5, 60_000, 100, 0, 0.0, "staged"),
     (1_000, 10, 12, 15_000, 600, 0, 0.0, "staged"),
     (1_000, 31, 20, 60_000, 128, 0, 0.3, "staged"),
-    (16_000, 1, 64, 100_000, 64, 0, 0.0, "atomic"),     # 65 columns: no lane each
+    (12_000, 1, 64, 50_000, 100, 0, 0.0, "atomic"),     # 65 columns: no lane each
     (2_000, 10, 5, 300, 64, 0, 0.0, "atomic"),
     (3_000, 16, 25, 2_000, 200, 0, 0.2, "atomic"),
     (70, 2, 0, 3_000, 385, 15, 0.0, "atomic"),

@@ -276,6 +276,7 @@ def test_step_route_refuses_invalid_arguments():
     ((1_024, 10, 5, 100_000, 300, 320), "staged"),     # 283 / 279, staged 118 / 117
     # a loss under uniform ids that the gain under Zipf ids outweighs
     ((16_384, 10, 15, 100_000, 300, 320), "pulled"),   # 1137 / 1042, pulled 616 / 1209
+    ((65_536, 10, 5, 100_000, 64, 64), "pulled"),      # 1424, pulled 593 (queue at the head rows)
 ])
 def test_step_route_weighs_both_distributions(shape, route):
     assert w2v.debug_step_route(*shape) == route
