@@ -145,3 +145,38 @@ def test_infinities_and_nans_stay_where_they_belong(B, N, K, V, D, route, srt):
         assert np.array_equal(np.isfinite(g), fin)
         assert scaled_error(g[fin], o[fin], S[fin]) <= BAR
     assert touched > 0
+
+
+@pytest.mark.parametrize("B,N,K,V,D,route", [
+    (10_000, 10, 5, 15_000, 300, "pulled"),
+    (1_500, 10, 5, 100_000, 300, "staged"),
+    (2_000, 10, 5, 300, 64, "atomic"),
+])
+def test_every_route_replays_from_a_graph(B, N, K, V, D, route):
+    """A captured call replayed with eager work in between: each replay leaves
+    what the eager call leaves (the atomic route's fp64 sums come in another
+    order: one fp32 step)."""
+    import torch
+    assert w2v.debug_step_route(B, N, K, V, D, D) == route
+    t, c, n = (to_dev(x) for x in inputs.kernel_batch(B, N, K, V, 1.0, 11))
+    start = [to_dev(inputs.init_matrix(V, D, "normal", s)) for s in (4, 5)]
+    want = [x.clone() for x in start]
+    ws = w2v.step_batch(t, c, n, want[0], want[1], 0.025)
+    m = [x.clone() for x in start]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        w2v.step_batch(t, c, n, m[0], m[1], 0.025, workspace=ws)
+    for _ in range(3):
+        for x, y in zip(m, start):
+            x.copy_(y)
+        other = [x.clone() for x in start]
+        w2v.step_batch(t, c, n, other[0], other[1], 0.025)   # eager, its own workspace
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for g, h in zip(m, want):
+            if route == "atomic":
+                g, h = g.cpu().numpy(), h.cpu().numpy()
+                assert np.all(np.abs(g - h) <= np.spacing(np.maximum(np.abs(g), np.abs(h))))
+            else:
+                assert torch.equal(g, h)
