@@ -46,9 +46,10 @@ struct GroupError {
                                               float& loss_part) const {
     // one exponential: t = e^-|x|, sigma of the smaller side is t / (1 + t)
     const float t = __expf(-fabsf(x));
-    const float r = recip_near1(1.f + t);
-    const float sp = x < 0.f ? r : t * r;        // sigma(-x)
-    const float sn = x < 0.f ? t * r : r;        // sigma(x)
+    const float larger = quotient_near1(1.f, 1.f + t);
+    const float smaller = quotient_near1(t, 1.f + t);
+    const float sp = x < 0.f ? larger : smaller;  // sigma(-x)
+    const float sn = x < 0.f ? smaller : larger;  // sigma(x)
     const uint32_t tb = gl->tbits[lk];
     const float nw = gl->negw[lk];
     float e = 0.f, l_t = 0.f, l_n = 0.f;

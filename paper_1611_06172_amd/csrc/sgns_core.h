@@ -391,18 +391,28 @@ __device__ __forceinline__ float reduce_tile(const F& value, int lane) {
   }
 }
 
-// 1 / x for x in [1, 4], within one ulp: the hardware's reciprocal and one
-// Newton step.
-__device__ __forceinline__ float recip_near1(float x) {
-  const float r = __builtin_amdgcn_rcpf(x);
-  return fmaf(r, fmaf(-x, r, 1.f), r);
+// a / d for a in [0, 1] and d in [1, 4]: the hardware's reciprocal, and the
+// quotient corrected by its residual (sigma of logits in [-1, 1]: 0.36 ulp off
+// in the mean; 0.39 as an IEEE divide 1 / (1 + e^-x), 0.41 as a corrected
+// reciprocal times a).
+__device__ __forceinline__ float quotient_near1(float a, float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  const float q = a * r;
+  return fmaf(fmaf(-d, q, a), r, q);
 }
 
 // log(1 + t) for t in [0, 1], within about an ulp: 2 atanh(s), s = t / (2 +
 // t) <= 1/3, by its series up to s^15 (the next term is below 2e-9 of the
-// sum).
+// sum). What the quotient and the sum 2 + t round away is added beside the
+// series, so that the last addition is the one that rounds (losses of logits
+// in [-1, 1]: 0.33 ulp off in the mean, as with the library's logarithm; 0.48
+// with a reciprocal times t).
 __device__ __forceinline__ float log1p_unit(float t) {
-  const float s = t * recip_near1(2.f + t);
+#pragma clang fp contract(off)  // `rest` belongs to s as rounded
+  const float d = 2.f + t;
+  const float r = __builtin_amdgcn_rcpf(d);
+  const float s = t * r;
+  const float rest = fmaf(-(t - (d - 2.f)), s, fmaf(-d, s, t)) * r;  // of t / (2 + t)
   const float q = s * s;
   float p = 1.f / 15.f;
   p = fmaf(p, q, 1.f / 13.f);
@@ -411,7 +421,7 @@ __device__ __forceinline__ float log1p_unit(float t) {
   p = fmaf(p, q, 1.f / 7.f);
   p = fmaf(p, q, 1.f / 5.f);
   p = fmaf(p, q, 1.f / 3.f);
-  return fmaf(2.f * s * q, p, 2.f * s);
+  return 2.f * (s + fmaf(s * q, p, rest));
 }
 
 // Error and loss of one slot of a minibatch of one target: column 0 is the
@@ -427,8 +437,7 @@ __device__ __forceinline__ float target_error(bool is_target, float x, float wgt
   // logarithm (a wavefront on its own spent a quarter of a minibatch here).
   const float z = is_target ? -x : x;
   const float t = __expf(-fabsf(z));
-  const float r = recip_near1(1.f + t);
-  const float sz = z < 0.f ? t * r : r;
+  const float sz = quotient_near1(z < 0.f ? t : 1.f, 1.f + t);
   if (want_loss) loss_part += wgt * (fmaxf(z, 0.f) + log1p_unit(t));
   return wgt * alpha * (is_target ? sz : -sz);
 }
